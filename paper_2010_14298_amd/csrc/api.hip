@@ -275,6 +275,7 @@ struct LinearWs {
   StatsSeg sx_seg, sw_seg, sg_seg;
   float *rmin, *rmax;
   int8_t *qx_t, *qw_t, *qg1_t, *qg2;
+  int64_t ldn, ldo;  // K pitches over the samples and over d_out
   int32_t *sum_x, *sum_w, *sum_g1, *sum_g2;
   float *sx, *zx, *sw, *zw, *sg1, *zg1, *sg2, *zg2;
   int32_t* perm;
@@ -288,6 +289,13 @@ struct LinearWs {
   double* colvec;
   double* colvec_part;
 };
+
+// K pitch of the contraction operands: whole 128-byte stages, the codes past
+// the matrix zero, so that any K takes the direct-to-LDS loop.  Both sides
+// measured at 3001 x 1024 -> 4096: the grad_W contraction over 3001 samples
+// takes 208 us on the register-staged loop (whose unaligned rows load byte by
+// byte); the padding adds at most 127 zero codes per row.
+int64_t k_pitch(int64_t n) { return (n + 127) / 128 * 128; }
 
 int linear_splits(int64_t N) { return (int)((N + MAX_K_CHUNK - 1) / MAX_K_CHUNK); }
 
@@ -304,10 +312,12 @@ LinearWs carve_linear(Carver& c, const float* X, const float* W, const float* G,
   w.rmin = c.take<float>(N);
   w.rmax = c.take<float>(N);
   stats_direct_rows(w.sg_seg, w.rmin, w.rmax);
-  w.qx_t = c.take<int8_t>(d_in * N);
-  w.qw_t = c.take<int8_t>(d_in * d_out);
-  w.qg1_t = c.take<int8_t>(d_out * N);
-  w.qg2 = c.take<int8_t>(N * d_out);
+  w.ldn = k_pitch(N);
+  w.ldo = k_pitch(d_out);
+  w.qx_t = c.take<int8_t>(d_in * w.ldn);
+  w.qw_t = c.take<int8_t>(d_in * w.ldo);
+  w.qg1_t = c.take<int8_t>(d_out * w.ldn);
+  w.qg2 = c.take<int8_t>(N * w.ldo);
   w.sum_x = c.take<int32_t>(d_in);
   w.sum_w = c.take<int32_t>(d_in);
   w.sum_g1 = c.take<int32_t>(d_out);
@@ -345,6 +355,7 @@ struct ForwardWs {
   Header h;
   StatsSeg sx_seg, sw_seg;
   int8_t *qx, *qw;
+  int64_t ldk;  // K pitch over d_in
   int32_t *sum_x, *sum_w;
   float *sx, *zx, *sw, *zw;
   int32_t* part;
@@ -358,8 +369,9 @@ ForwardWs carve_forward(Carver& c, const float* X, const float* W, int64_t N, in
   w.sw_seg = stats_flat_seg(W, d_out * d_in);
   w.sx_seg.part = c.take<float2>(stats_partials(w.sx_seg));
   w.sw_seg.part = c.take<float2>(stats_partials(w.sw_seg));
-  w.qx = c.take<int8_t>(N * d_in);
-  w.qw = c.take<int8_t>(d_out * d_in);
+  w.ldk = k_pitch(d_in);
+  w.qx = c.take<int8_t>(N * w.ldk);
+  w.qw = c.take<int8_t>(d_out * w.ldk);
   w.sum_x = c.take<int32_t>(N);
   w.sum_w = c.take<int32_t>(d_out);
   w.sx = c.take<float>(1);
@@ -693,8 +705,11 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   Carver c(ws);
   LinearWs w = carve_linear(c, X, W, G, N, d_in, d_out, *cfg);
   // caller buffers for the gradient codes (and the BHQ permutation)
+  // without padding: a K that is no whole number of stages then takes the
+  // register-staged loop
   if (cfg->qb2_codes) w.qg2 = cfg->qb2_codes;
   if (cfg->qb1_codes) w.qg1_t = cfg->qb1_codes;
+  const int64_t ldg1 = cfg->qb1_codes ? N : w.ldn;
   if (cfg->perm && w.perm) w.perm = cfg->perm;
   const fqt_qspec qx = cfg->qb_x;
   const bool bhq = qx.kind == FQT_BHQ;
@@ -754,6 +769,7 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   px.scale = w.sx;
   px.zero = w.zx;
   px.q_t = w.qx_t;
+  px.ldt = w.ldn;
   px.sum_t = w.sum_x;
   // Q_theta(W): deterministic PTQ, codes [d_in, d_out]
   QuantParams pw{};
@@ -764,6 +780,7 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   pw.scale = w.sw;
   pw.zero = w.zw;
   pw.q_t = w.qw_t;
+  pw.ldt = w.ldo;
   pw.sum_t = w.sum_w;
   QuantParams pg{};
   pg.x = G;
@@ -782,12 +799,15 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   // grad_X contraction's loader
   const bool packed = cfg->packed_codes == 1 && qx.bits <= 4 && d_out % 16 == 0;
   pg.packed = packed ? 1 : 0;
+  const int64_t ldg2 = packed || cfg->qb2_codes ? d_out : w.ldo;
+  pg.ldn = ldg2 > d_out ? ldg2 : 0;
   pg.bits2 = cfg->qb_w.bits;
   pg.stream2 = 0;
   pg.scale2 = w.sg1;
   pg.zero2 = w.zg1;
   pg.shift2 = w.shift1;
   pg.q2_t = w.qg1_t;
+  pg.ldt = ldg1 > N ? ldg1 : 0;
   pg.sum2_t = w.sum_g1;
   if (bhq) {
     st = bhq_params(w.bhq, G, N, d_out, qx.block_size, w.perm, w.sg2, pg, s);
@@ -809,6 +829,7 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
     cv.q_t = w.qx_t;
     cv.rows = N;
     cv.cols = d_in;
+    cv.ldq = w.ldn;
     cv.perm = w.perm;
     cv.zeta = w.zeta1;
     cv.scaleX = w.sx;
@@ -827,10 +848,11 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   gw.M = d_out;
   gw.N = d_in;
   gw.K = N;
-  gw.lda = N;
-  gw.ldb = N;
+  gw.Kp = ldg1;
+  gw.lda = ldg1;
+  gw.ldb = w.ldn;
   gw.splits = w.splits;
-  gw.kchunk = w.splits > 1 ? MAX_K_CHUNK : N;
+  gw.kchunk = w.splits > 1 ? MAX_K_CHUNK : gw.Kp;
   gw.part = w.part;
   gw.out = grad_W;
   gw.ldo = d_in;
@@ -863,11 +885,12 @@ fqt_status fqt_linear_backward(const float* X, const float* W, const float* G, i
   gx.M = N;
   gx.N = d_in;
   gx.K = d_out;
-  gx.lda = packed ? d_out / 2 : d_out;
+  gx.Kp = ldg2;
+  gx.lda = packed ? d_out / 2 : ldg2;
   gx.packedA = packed ? 1 : 0;
-  gx.ldb = d_out;
+  gx.ldb = w.ldo;
   gx.splits = 1;
-  gx.kchunk = d_out;
+  gx.kchunk = gx.Kp;
   gx.out = grad_X;
   gx.ldo = d_in;
   gx.perm = w.perm;
@@ -960,8 +983,8 @@ fqt_status fqt_linear_forward(const float* X, const float* W, int64_t N, int64_t
   px.scale = w.sx;
   px.zero = w.zx;
   px.q_nat = w.qx;
+  px.ldn = w.ldk;
   px.sum_nat = w.sum_x;
-  FQT_TRY(launch_quant(px, QM_TENSOR, s));
   QuantParams pw{};
   pw.x = W;
   pw.rows = d_out;
@@ -970,8 +993,9 @@ fqt_status fqt_linear_forward(const float* X, const float* W, int64_t N, int64_t
   pw.scale = w.sw;
   pw.zero = w.zw;
   pw.q_nat = w.qw;
+  pw.ldn = w.ldk;
   pw.sum_nat = w.sum_w;
-  FQT_TRY(launch_quant(pw, QM_TENSOR, s));
+  FQT_TRY(launch_quant_nat_pair(px, pw, s));
   // Y = Q_f(X) Q_theta(W)^T: contraction over d_in, per-tensor epilogue
   GemmParams g{};
   g.A = w.qx;
@@ -979,10 +1003,11 @@ fqt_status fqt_linear_forward(const float* X, const float* W, int64_t N, int64_t
   g.M = N;
   g.N = d_out;
   g.K = d_in;
-  g.lda = d_in;
-  g.ldb = d_in;
+  g.Kp = w.ldk;
+  g.lda = w.ldk;
+  g.ldb = w.ldk;
   g.splits = w.splits;
-  g.kchunk = w.splits > 1 ? MAX_K_CHUNK : d_in;
+  g.kchunk = w.splits > 1 ? MAX_K_CHUNK : g.Kp;
   g.part = w.part;
   g.out = Y;
   g.ldo = d_out;

@@ -185,6 +185,8 @@ struct QuantParams {
   const float* zero;
   int8_t* q_nat;       // [rows, cols] slot order, or nullptr (packed: [rows, cols / 2] bytes)
   int packed;          // natural codes of bits <= 4 stored two per byte (float4 rows only)
+  int64_t ldn;         // row pitch of q_nat (0: cols, no padding); codes past cols are zero
+  int64_t ldt;         // row pitch of q_t / q2_t (0: rows, no padding); codes past rows are zero
   int64_t pm_o;        // > 0: natural codes pixel-major, column j of row (slot) i at
                        // ((j / pm_o) rows + i) pm_o + j % pm_o (cols % pm_o == 0, pm_o % 4 == 0)
   int32_t* sum_nat;    // [rows] row sums, or nullptr
@@ -212,11 +214,10 @@ enum QuantMode { QM_TENSOR = 0, QM_ROW = 1, QM_BHQ = 2 };
 hipError_t launch_quant(const QuantParams& p, int mode, hipStream_t s);
 // The seed batch of one quantizer (natural layout, cols % 4 == 0).
 hipError_t launch_quant_seeds(const QuantParams& p, int mode, hipStream_t s);
-// Two per-tensor quantizations with transposed outputs only, one launch.
-hipError_t launch_quant_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s);
+// Two per-tensor quantizations with natural outputs only, one launch.
+hipError_t launch_quant_nat_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s);
 // The gradient quantizer pg (with its transposed second quantizer) and the
-// per-tensor transposed quantizers px, pw in one launch when the shapes
-// allow it, else as separate launches.
+// per-tensor transposed quantizers px, pw in one launch.
 hipError_t launch_quant_fused(const QuantParams& pg, int mode, const QuantParams& px, const QuantParams& pw,
                               hipStream_t s);
 
@@ -260,6 +261,7 @@ struct GemmParams {
   int packedA;      // A holds codes of at most 4 bits two per byte (as the quantizer packs them), K % 16 == 0
   const int8_t* B;  // [N, K] row stride ldb
   int64_t M, N, K, lda, ldb;
+  int64_t Kp;       // K with the zero codes that pad both operands' rows (0: K, no padding)
   // conv B row map (bmap_c > 0, fast K loop only): row j = (tap, c) with
   // tap = (r, s) of a bmap_kw-wide kernel starts at B + (s bmap_c + c) ldb +
   // r bmap_wp (shifted activation-code grids, see ConvGeom)
@@ -297,11 +299,12 @@ hipError_t launch_splitk_reduce(const GemmParams& p, int64_t* out64, int epi, hi
 
 // Zero-point term of a contraction over samples whose A rows (samples) carry
 // their own zero points: v[c] = sum_n zeta_n Xt[n, c] (zeta_n = half / s_n +
-// z_n from the finalize), Xt[n, c] = dx q[c, n] + zx (q: [cols, rows]
+// z_n from the finalize), Xt[n, c] = dx q[c, n] + zx (q: [cols, ldq]
 // transposed codes in slot order, perm slot -> row or nullptr), float64.
 struct ColvecParams {
   const int8_t* q_t;
   int64_t rows, cols;
+  int64_t ldq;          // row pitch of q_t, a multiple of 16
   const int32_t* perm;
   const double* zeta;   // zeta_n [rows], source-row order
   const float* scaleX;  // [1]

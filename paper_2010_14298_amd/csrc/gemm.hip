@@ -80,7 +80,8 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
   const int64_t m0 = (tile / tiles_n) * C::BM;
   const int64_t n0 = (tile % tiles_n) * C::BN;
   const int64_t kbeg = (int64_t)split * p.kchunk;
-  const int64_t kend = (kbeg + p.kchunk < p.K) ? kbeg + p.kchunk : p.K;
+  const int64_t Kp = p.Kp > 0 ? p.Kp : p.K;
+  const int64_t kend = (kbeg + p.kchunk < Kp) ? kbeg + p.kchunk : Kp;
   const int lrow = lane & 31;
 
   v16i acc[C::IT][C::JT];
@@ -374,7 +375,7 @@ __global__ void splitk_reduce_kernel(GemmParams p, int64_t* out64, int epi) {
 // its lanes and stores part[y][c] (and the zeta sum in part[y][cols], from
 // x = 0).  The reduce adds the partials of each column in order of y.
 // ---------------------------------------------------------------------------
-constexpr int COLVEC_C = 64;
+constexpr int COLVEC_C = 16;
 constexpr int COLVEC_N = 1024;
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
@@ -388,7 +389,6 @@ __global__ __launch_bounds__(256) void colvec_partial_kernel(ColvecParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t cw = (int64_t)blockIdx.x * COLVEC_C + wave * CW;
   const int64_t n0 = (int64_t)blockIdx.y * COLVEC_N + 16 * lane;
-  const bool full = n0 + 16 <= p.rows && (p.rows & 15) == 0;
   double z[16], zs = 0.0;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
@@ -402,18 +402,9 @@ __global__ __launch_bounds__(256) void colvec_partial_kernel(ColvecParams p) {
 #pragma unroll
   for (int c = 0; c < CW; ++c) {
     const int64_t col = cw + c;
-    const int8_t* q = p.q_t + col * p.rows + n0;
-    if (col >= p.cols) {
-      v[c] = make_uint4(0u, 0u, 0u, 0u);
-    } else if (full) {
-      v[c] = *reinterpret_cast<const uint4*>(q);
-    } else {
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-        if (n0 + k < p.rows) w[k >> 2] |= (uint32_t)(uint8_t)q[k] << (8 * (k & 3));
-      v[c] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+    const bool in = col < p.cols && n0 < p.ldq;  // the pitch is whole 16-byte runs
+    const uint4 q = *reinterpret_cast<const uint4*>(p.q_t + (in ? col * p.ldq + n0 : 0));
+    v[c] = in ? q : make_uint4(0u, 0u, 0u, 0u);
   }
 #pragma unroll
   for (int c = 0; c < CW; ++c) {
@@ -447,6 +438,7 @@ int64_t colvec_splits(int64_t rows) { return (rows + COLVEC_N - 1) / COLVEC_N; }
 
 hipError_t launch_colvec(const ColvecParams& p, hipStream_t s) {
   const int64_t cb = (p.cols + COLVEC_C - 1) / COLVEC_C, ns = colvec_splits(p.rows);
+  if (p.ldq < p.rows || (p.ldq & 15) != 0 || ((uintptr_t)p.q_t & 15) != 0) return hipErrorInvalidValue;
   if (p.cols < 1 || p.rows < 1 || cb > 0x7FFFFFFF || ns > 65535) return hipErrorInvalidValue;
   hipLaunchKernelGGL(colvec_partial_kernel, dim3((unsigned)cb, (unsigned)ns), dim3(256), 0, s, p);
   hipLaunchKernelGGL(colvec_reduce_kernel, dim3((unsigned)((p.cols + 255) / 256)), dim3(256), 0, s, p, ns);
@@ -472,7 +464,7 @@ static hipError_t launch_gemm_t(GemmParams p, hipStream_t s) {
   const int64_t tiles = gemm_tiles<C>(p.M, p.N);
   if (tiles > 0x7FFFFFFF || p.splits > 65535) return hipErrorInvalidValue;
   // fast K loop: aligned rows, whole stages per split
-  const bool whole = (p.kchunk % C::BK == 0) && (p.K % C::BK == 0);
+  const bool whole = (p.kchunk % C::BK == 0) && ((p.Kp > 0 ? p.Kp : p.K) % C::BK == 0);
   const bool fast = ((p.lda & 15) == 0) && ((p.ldb & 15) == 0) && (((uintptr_t)p.A & 15) == 0) &&
                     (((uintptr_t)p.B & 15) == 0) && whole;
   const dim3 grid((unsigned)tiles, (unsigned)p.splits);

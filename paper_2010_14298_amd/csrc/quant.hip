@@ -668,6 +668,9 @@ constexpr int QT_ROWS_PER_WAVE = 16;
 // y, in the top-byte form of sr_top / rne_top: stochastic rounding with the
 // Philox blocks of elements e0 .. e0 + 3 (VEC: the argument is the block
 // index e0 / 4 of the one block that holds all four) or round-half-even.
+// Without VEC the four elements straddle two blocks at the offset ph = e0 % 4,
+// the same in every lane (the columns of a lane start at a multiple of 4), so
+// two blocks serve all four elements, and one when ph = 0.
 template <bool VEC>
 __device__ __forceinline__ void sr4(const float (&y)[4], uint64_t e0, uint64_t seed, uint32_t stream, float Bf,
                                     uint32_t hoff, int32_t (&t)[4]) {
@@ -678,14 +681,29 @@ __device__ __forceinline__ void sr4(const float (&y)[4], uint64_t e0, uint64_t s
     t[2] = sr_top(y[2], o.z, Bf, hoff);
     t[3] = sr_top(y[3], o.w, Bf, hoff);
   } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint64_t e = e0 + j;
-      const u32x4 o = philox_block(e, seed, stream);
-      t[j] = sr_top(y[j], philox_word(o, (int)(e & 3)), Bf, hoff);
+    const int ph = __builtin_amdgcn_readfirstlane((int)(e0 & 3));
+    const u32x4 a = philox_of_block(e0 >> 2, seed, stream);
+    u32x4 w = a;
+    if (ph != 0) {
+      const u32x4 b = philox_of_block((e0 >> 2) + 1, seed, stream);
+      if (ph == 1)
+        w = u32x4{a.y, a.z, a.w, b.x};
+      else if (ph == 2)
+        w = u32x4{a.z, a.w, b.x, b.y};
+      else
+        w = u32x4{a.w, b.x, b.y, b.z};
     }
+    t[0] = sr_top(y[0], w.x, Bf, hoff);
+    t[1] = sr_top(y[1], w.y, Bf, hoff);
+    t[2] = sr_top(y[2], w.z, Bf, hoff);
+    t[3] = sr_top(y[3], w.w, Bf, hoff);
   }
 }
+// Four consecutive floats at 4-byte alignment (one 16-byte load: global
+// memory takes multi-dword loads at dword alignment).
+struct __attribute__((packed, aligned(4))) Float4U {
+  float x, y, z, w;
+};
 __device__ __forceinline__ void rne4(const float (&y)[4], float Bf, uint32_t hoff, int32_t (&t)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) t[j] = rne_top(y[j], Bf, hoff);
@@ -759,8 +777,16 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
         for (int j = 0; j < 4; ++j) g[r][j] = 0.0f;
       }
     } else {
+      if (ok && c0 + 3 < cols) {
+        const Float4U v = *reinterpret_cast<const Float4U*>(xr + c0);
+        g[r][0] = v.x;
+        g[r][1] = v.y;
+        g[r][2] = v.z;
+        g[r][3] = v.w;
+      } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) g[r][j] = (ok && c0 + j < cols) ? xr[c0 + j] : 0.0f;
+        for (int j = 0; j < 4; ++j) g[r][j] = (ok && c0 + j < cols) ? xr[c0 + j] : 0.0f;
+      }
     }
   }
 
@@ -773,6 +799,16 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
     if (sl < rows) {
       lscale = p.scale[sl];
       lzero = p.zero[sl];
+    }
+  }
+  // the per-row scale, zero and shift of a second quantizer, the same way
+  float lscale2 = 1.0f, lzero2 = 0.0f;
+  int lshift2 = 0;
+  if constexpr (H2 == 2) {
+    if ((lane & 15) < nok) {
+      lscale2 = p.scale2[lrow];
+      lzero2 = p.zero2[lrow];
+      lshift2 = p.shift2[lrow];
     }
   }
   auto row_scale = [&](int r) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lscale), r)); };
@@ -837,8 +873,13 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
   // pixel-major natural codes: this lane's four columns lie in one pixel of pm_o channels
   // natural codes of row r go to nat0 + r * nat_step (bytes; with packed
   // codes to nat0 / 2 + r * nat_step / 2, cols % 4 == 0)
-  const int64_t nat0 = p.pm_o > 0 ? (c0 / p.pm_o) * rows * p.pm_o + c0 % p.pm_o + slot0 * p.pm_o : slot0 * cols + c0;
-  const int64_t nat_step = p.pm_o > 0 ? p.pm_o : cols;
+  const int64_t ldn = p.ldn > 0 ? p.ldn : cols;
+  const int64_t nat0 = p.pm_o > 0 ? (c0 / p.pm_o) * rows * p.pm_o + c0 % p.pm_o + slot0 * p.pm_o : slot0 * ldn + c0;
+  const int64_t nat_step = p.pm_o > 0 ? p.pm_o : ldn;
+  // whole words of natural codes: always with VEC; else rows padded with zero
+  // codes to a pitch of whole words
+  const bool nat_word = VEC || p.ldn > 0;
+  const bool nat_ok = c0 < (p.ldn > 0 ? p.ldn : cols);
   int32_t rs4[4];                // per-lane partial row sums of the natural codes, 4 rows at a time
   uint32_t tq[4][4], tq2[4][4];  // transposed codes: [column][4 words of 16 slots]; rows past the end stay 0
 #pragma unroll
@@ -1008,12 +1049,9 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
       float s2r = s2, z2r = z2;
       int sh2 = 0;
       if constexpr (H2 == 2) {
-        if (ok) {
-          const int32_t sr = src_row(r);
-          s2r = p.scale2[sr];
-          z2r = p.zero2[sr];
-          sh2 = p.shift2[sr];
-        }
+        s2r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lscale2), r));
+        z2r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lzero2), r));
+        sh2 = __builtin_amdgcn_readlane(lshift2, r);
       }
       float y2[4];
 #pragma unroll
@@ -1031,17 +1069,17 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
     }
     if constexpr (!TRANS) {
       const uint32_t w = pack_top4(t[0], t[1], t[2], t[3]);
-      if (p.q_nat && ok && lane_ok) {
+      if (p.q_nat && ok && nat_ok) {
         int8_t* dst = p.q_nat + nat0 + r * nat_step;
-        if (VEC && p.packed) {
+        if (p.packed) {
           // codes of at most 4 bits, two per byte: the nibble of column 2i is
           // the low half of byte i, the code stored as q + 8 in [0, 15]
           const uint32_t nb = (w ^ 0x08080808u) & 0x0F0F0F0Fu;
           const uint32_t x2 = nb | (nb >> 4);
           const uint32_t pk = __builtin_amdgcn_perm(0u, x2, 0x0c0c0200u);  // bytes 0 and 2 of x2
           *reinterpret_cast<uint16_t*>(p.q_nat + nat0 / 2 + r * (nat_step / 2)) = (uint16_t)pk;
-        } else if constexpr (VEC) {
-          *reinterpret_cast<uint32_t*>(dst) = w;
+        } else if (nat_word) {
+          *reinterpret_cast<uint32_t*>(dst) = w & colmask;
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
@@ -1061,30 +1099,32 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
     }
   }
 
-  // ---- transposed stores: 16 consecutive slots per column
-  const bool tvec = ((rows & 15) == 0) && nok == QT_ROWS_PER_WAVE;
+  // ---- transposed stores: 16 consecutive slots per column (with a padded
+  // pitch the slots past the last row are zero codes)
+  const int64_t ldt = p.ldt > 0 ? p.ldt : rows;
+  const bool tvec = p.ldt > 0 ? slot0 < p.ldt : ((rows & 15) == 0) && nok == QT_ROWS_PER_WAVE;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int64_t col = c0 + j;
     if (col >= cols) continue;
     if constexpr (TRANS) {
-      int8_t* dst = p.q_t + col * rows + slot0;
+      int8_t* dst = p.q_t + col * ldt + slot0;
       if (tvec) {
         *reinterpret_cast<uint4*>(dst) = make_uint4(tq[j][0], tq[j][1], tq[j][2], tq[j][3]);
       } else {
 #pragma unroll
         for (int r = 0; r < QT_ROWS_PER_WAVE; ++r)
-          if (r < nok) dst[r] = (int8_t)((tq[j][r >> 2] >> (8 * (r & 3))) & 255);
+          if (p.ldt == 0 && r < nok) dst[r] = (int8_t)((tq[j][r >> 2] >> (8 * (r & 3))) & 255);
       }
     }
     if constexpr (H2 != 0) {
-      int8_t* dst = p.q2_t + col * rows + slot0;
+      int8_t* dst = p.q2_t + col * ldt + slot0;
       if (tvec) {
         *reinterpret_cast<uint4*>(dst) = make_uint4(tq2[j][0], tq2[j][1], tq2[j][2], tq2[j][3]);
       } else {
 #pragma unroll
         for (int r = 0; r < QT_ROWS_PER_WAVE; ++r)
-          if (r < nok) dst[r] = (int8_t)((tq2[j][r >> 2] >> (8 * (r & 3))) & 255);
+          if (p.ldt == 0 && r < nok) dst[r] = (int8_t)((tq2[j][r >> 2] >> (8 * (r & 3))) & 255);
       }
     }
   }
@@ -1119,22 +1159,9 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
 }
 
 
-template <int MODE, int K, int H2, bool VEC, bool TRANS>
+template <int MODE, int K, bool VEC, bool TRANS>
 __global__ __launch_bounds__(256) void quant_tile_kernel(QuantParams p) {
-  quant_tile<MODE, K, H2, VEC, TRANS>(p, blockIdx.x, blockIdx.y);
-}
-
-// Two independent per-tensor transposed quantizations in one launch (Q_f(X)
-// and Q_theta(W)): blocks [0, nb0) tile the first, the rest the second, each
-// over a row-major grid of ct column tiles.
-template <bool VEC>
-__global__ __launch_bounds__(256) void quant_tile2_kernel(QuantParams p0, QuantParams p1, int64_t nb0, int64_t ct0,
-                                                          int64_t ct1) {
-  const int64_t b = blockIdx.x;
-  if (b < nb0)
-    quant_tile<QM_TENSOR, 0, 0, VEC, true>(p0, b % ct0, b / ct0);
-  else
-    quant_tile<QM_TENSOR, 0, 0, VEC, true>(p1, (b - nb0) % ct1, (b - nb0) / ct1);
+  quant_tile<MODE, K, 0, VEC, TRANS>(p, blockIdx.x, blockIdx.y);
 }
 
 // The gradient pass (natural codes plus the transposed Q_b1) and the two
@@ -1142,7 +1169,7 @@ __global__ __launch_bounds__(256) void quant_tile2_kernel(QuantParams p0, QuantP
 // period-th block (while they last) is an X / W tile, so that those
 // memory-light tiles interleave with the arithmetic-heavy gradient tiles;
 // the other blocks take the gradient tiles in order.
-template <int MODE, int K, int H2>
+template <int MODE, int K, int H2, bool VEC>
 __global__ __launch_bounds__(256) void quant_fused_kernel(QuantParams pg, QuantParams px, QuantParams pw, int64_t nbx,
                                                           int64_t nbw, int64_t period, int64_t ctg, int64_t ctx,
                                                           int64_t ctw) {
@@ -1151,42 +1178,72 @@ __global__ __launch_bounds__(256) void quant_fused_kernel(QuantParams pg, QuantP
   if (b % period == period - 1 && b / period < nxw) {
     const int64_t t = b / period;
     if (t < nbx)
-      quant_tile<QM_TENSOR, 0, 0, true, true>(px, t % ctx, t / ctx);
+      quant_tile<QM_TENSOR, 0, 0, VEC, true>(px, t % ctx, t / ctx);
     else
-      quant_tile<QM_TENSOR, 0, 0, true, true>(pw, (t - nbx) % ctw, (t - nbx) / ctw);
+      quant_tile<QM_TENSOR, 0, 0, VEC, true>(pw, (t - nbx) % ctw, (t - nbx) / ctw);
   } else {
     const int64_t before = (b + 1) / period < nxw ? (b + 1) / period : nxw;
     const int64_t t = b - before;
-    quant_tile<MODE, K, H2, true, false>(pg, t % ctg, t / ctg);
+    quant_tile<MODE, K, H2, VEC, false>(pg, t % ctg, t / ctg);
   }
 }
 
-template <int MODE, int K>
-static hipError_t launch_quant_fused_k(const QuantParams& pg, const QuantParams& px, const QuantParams& pw,
+// Slot tiles of a quantization: the rows, and the zero codes of a padded
+// transposed pitch.
+static int64_t slot_tiles(const QuantParams& p) {
+  const int64_t slots = p.ldt > p.rows ? p.ldt : p.rows;
+  return (slots + QT_SLOTS - 1) / QT_SLOTS;
+}
+// Column tiles: the pitch of padded natural codes ends inside the last tile
+// (checked in pitch_ok).
+static int64_t col_tiles(const QuantParams& p) { return (p.cols + QT_COLS - 1) / QT_COLS; }
+// Pitches (0: none): whole 16-slot runs, resp. whole words inside the last
+// column tile, next to an aligned destination.
+static bool pitch_ok(const QuantParams& p) {
+  if (p.ldt != 0 && (p.ldt < p.rows || (p.ldt & 15) != 0 || (((uintptr_t)p.q_t | (uintptr_t)p.q2_t) & 15) != 0))
+    return false;
+  if (p.ldn != 0 && (p.ldn < p.cols || (p.ldn & 3) != 0 || p.ldn > col_tiles(p) * QT_COLS || p.packed || p.pm_o ||
+                     ((uintptr_t)p.q_nat & 3) != 0))
+    return false;
+  return true;
+}
+
+template <int MODE, int K, bool VEC>
+static hipError_t launch_quant_fused_v(const QuantParams& pg, const QuantParams& px, const QuantParams& pw,
                                        hipStream_t s) {
-  const int64_t ctg = (pg.cols + QT_COLS - 1) / QT_COLS, rtg = (pg.rows + QT_SLOTS - 1) / QT_SLOTS;
-  const int64_t ctx = (px.cols + QT_COLS - 1) / QT_COLS, rtx = (px.rows + QT_SLOTS - 1) / QT_SLOTS;
-  const int64_t ctw = (pw.cols + QT_COLS - 1) / QT_COLS, rtw = (pw.rows + QT_SLOTS - 1) / QT_SLOTS;
+  if (!pitch_ok(pg) || !pitch_ok(px) || !pitch_ok(pw)) return hipErrorInvalidValue;
+  const int64_t ctg = col_tiles(pg), rtg = slot_tiles(pg);
+  const int64_t ctx = col_tiles(px), rtx = slot_tiles(px);
+  const int64_t ctw = col_tiles(pw), rtw = slot_tiles(pw);
   const int64_t nbg = ctg * rtg, nbx = ctx * rtx, nbw = ctw * rtw;
   const int64_t nb = nbg + nbx + nbw;
   if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
   const int64_t period = nb / (nbx + nbw);
   if (pg.shift2)
-    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 2>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
+    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 2, VEC>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
                        period, ctg, ctx, ctw);
   else
-    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 1>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
+    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 1, VEC>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
                        period, ctg, ctx, ctw);
   return hipGetLastError();
 }
 
+// Rows of whole float4s (and one Philox block per lane and row), or the
+// general tiles when any of the three matrices has none.
+static bool quant_vec(const QuantParams& p) { return (p.cols % 4 == 0) && (((uintptr_t)p.x & 15) == 0); }
+template <int MODE, int K>
+static hipError_t launch_quant_fused_k(const QuantParams& pg, const QuantParams& px, const QuantParams& pw,
+                                       hipStream_t s) {
+  if (quant_vec(pg) && quant_vec(px) && quant_vec(pw)) return launch_quant_fused_v<MODE, K, true>(pg, px, pw, s);
+  return launch_quant_fused_v<MODE, K, false>(pg, px, pw, s);
+}
+
 template <int MODE, int K>
 static hipError_t launch_quant_k(const QuantParams& p, hipStream_t s) {
-  const int64_t ct = (p.cols + QT_COLS - 1) / QT_COLS;
-  const int64_t rt = (p.rows + QT_SLOTS - 1) / QT_SLOTS;
-  if (ct > 0x7FFFFFFF || rt > 65535) return hipErrorInvalidValue;
+  const int64_t ct = col_tiles(p), rt = slot_tiles(p);
+  if (ct > 0x7FFFFFFF || rt > 65535 || !pitch_ok(p)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)ct, (unsigned)rt);
-  const bool vec = (p.cols % 4 == 0) && (((uintptr_t)p.x & 15) == 0);
+  const bool vec = quant_vec(p);
   if (p.packed && (!vec || p.bits > 4 || p.q_t)) return hipErrorInvalidValue;
   // one primary layout: natural (with an optional transposed Q_b1) or transposed
   if ((p.q_nat || p.sum_nat) && (p.q_t || p.sum_t)) return hipErrorInvalidValue;
@@ -1194,61 +1251,54 @@ static hipError_t launch_quant_k(const QuantParams& p, hipStream_t s) {
     return hipErrorInvalidValue;
   const bool trans = p.q_t || p.sum_t;
   if (p.shift && MODE != QM_ROW) return hipErrorInvalidValue;
-  if (p.q2_t) {
-    if (trans || !p.stoch) return hipErrorInvalidValue;
-    if (p.shift2) {
-      if (vec)
-        hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 2, true, false>), grid, dim3(256), 0, s, p);
-      else
-        hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 2, false, false>), grid, dim3(256), 0, s, p);
-    } else if (vec) {
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 1, true, false>), grid, dim3(256), 0, s, p);
-    } else {
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 1, false, false>), grid, dim3(256), 0, s, p);
-    }
-  } else if (trans) {
+  if (p.q2_t) return hipErrorInvalidValue;  // launch_quant_fused
+  if (trans) {
     if (vec)
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 0, true, true>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, true, true>), grid, dim3(256), 0, s, p);
     else
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 0, false, true>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, false, true>), grid, dim3(256), 0, s, p);
   } else {
     if (vec)
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 0, true, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, true, false>), grid, dim3(256), 0, s, p);
     else
-      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, 0, false, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((quant_tile_kernel<MODE, K, false, false>), grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_quant_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s) {
-  for (const QuantParams* p : {&p0, &p1})
-    if (p->q_nat || p->sum_nat || p->q2_t || !p->q_t) return hipErrorInvalidValue;
-  const int64_t ct0 = (p0.cols + QT_COLS - 1) / QT_COLS, rt0 = (p0.rows + QT_SLOTS - 1) / QT_SLOTS;
-  const int64_t ct1 = (p1.cols + QT_COLS - 1) / QT_COLS, rt1 = (p1.rows + QT_SLOTS - 1) / QT_SLOTS;
-  const int64_t nb0 = ct0 * rt0, nb = nb0 + ct1 * rt1;
-  if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const bool vec = (p0.cols % 4 == 0) && (((uintptr_t)p0.x & 15) == 0) && (p1.cols % 4 == 0) &&
-                   (((uintptr_t)p1.x & 15) == 0);
-  if (vec)
-    hipLaunchKernelGGL(quant_tile2_kernel<true>, dim3((unsigned)nb), dim3(256), 0, s, p0, p1, nb0, ct0, ct1);
+// Two per-tensor quantizations with natural outputs (Q_f(X) and Q_theta(W) of
+// the layer forward) in one launch: blocks [0, nb0) tile the first, the rest
+// the second, each over a row-major grid of ct column tiles.
+template <bool VEC>
+__global__ __launch_bounds__(256) void quant_nat2_kernel(QuantParams p0, QuantParams p1, int64_t nb0, int64_t ct0,
+                                                         int64_t ct1) {
+  const int64_t b = blockIdx.x;
+  if (b < nb0)
+    quant_tile<QM_TENSOR, 0, 0, VEC, false>(p0, b % ct0, b / ct0);
   else
-    hipLaunchKernelGGL(quant_tile2_kernel<false>, dim3((unsigned)nb), dim3(256), 0, s, p0, p1, nb0, ct0, ct1);
+    quant_tile<QM_TENSOR, 0, 0, VEC, false>(p1, (b - nb0) % ct1, (b - nb0) / ct1);
+}
+
+hipError_t launch_quant_nat_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s) {
+  for (const QuantParams* p : {&p0, &p1})
+    if (!p->q_nat || p->q_t || p->sum_t || p->q2_t || p->packed || p->pm_o || !pitch_ok(*p)) return hipErrorInvalidValue;
+  const int64_t ct0 = col_tiles(p0), ct1 = col_tiles(p1);
+  const int64_t nb0 = ct0 * slot_tiles(p0), nb = nb0 + ct1 * slot_tiles(p1);
+  if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (quant_vec(p0) && quant_vec(p1))
+    hipLaunchKernelGGL(quant_nat2_kernel<true>, dim3((unsigned)nb), dim3(256), 0, s, p0, p1, nb0, ct0, ct1);
+  else
+    hipLaunchKernelGGL(quant_nat2_kernel<false>, dim3((unsigned)nb), dim3(256), 0, s, p0, p1, nb0, ct0, ct1);
   return hipGetLastError();
 }
 
 hipError_t launch_quant_fused(const QuantParams& pg, int mode, const QuantParams& px, const QuantParams& pw,
                               hipStream_t s) {
-  // float4 rows everywhere, natural + transposed Q_b1 for the gradient,
-  // transposed only for X and W; anything else goes out as three launches
-  auto vec = [](const QuantParams& p) { return (p.cols % 4 == 0) && (((uintptr_t)p.x & 15) == 0); };
-  if (pg.packed && (!vec(pg) || pg.bits > 4)) return hipErrorInvalidValue;
-  const bool shape = vec(pg) && vec(px) && vec(pw) && pg.q2_t && pg.stoch && !pg.q_t && !pg.sum_t && !px.q_nat &&
-                     !px.sum_nat && !px.q2_t && px.q_t && !pw.q_nat && !pw.sum_nat && !pw.q2_t && pw.q_t;
-  if (!shape) {
-    hipError_t e = launch_quant_pair(px, pw, s);
-    if (e != hipSuccess) return e;
-    return launch_quant(pg, mode, s);
-  }
+  // natural + transposed Q_b1 for the gradient, transposed only for X and W
+  if (pg.packed && (!quant_vec(pg) || pg.bits > 4)) return hipErrorInvalidValue;
+  const bool shape = pg.q2_t && pg.stoch && !pg.q_t && !pg.sum_t && !px.q_nat && !px.sum_nat && !px.q2_t && px.q_t &&
+                     !pw.q_nat && !pw.sum_nat && !pw.q2_t && pw.q_t;
+  if (!shape) return hipErrorInvalidValue;
   if (mode == QM_TENSOR) return launch_quant_fused_k<QM_TENSOR, 0>(pg, px, pw, s);
   if (mode == QM_ROW) return launch_quant_fused_k<QM_ROW, 0>(pg, px, pw, s);
   switch (pg.L.k) {
