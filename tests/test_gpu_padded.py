@@ -1,0 +1,82 @@
+"""Contraction operands whose K is no whole number of 128-byte stages (padded
+with zero codes), rows that are no whole number of float4s, and inputs off
+their 16-byte alignment: gradients and activations within 1e-5 row-normwise of
+the oracle's float64 products, and exported codes bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import backward as BW
+from oracle import chain as CH
+from oracle import quantizers as Q
+from paper_2010_14298_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+REL_TOL = 1e-5
+
+
+def fqt():
+    from paper_2010_14298_amd import fqt as f
+    f.load()
+    return f
+
+
+def dev(x, shift=0):
+    """A contiguous device copy, `shift` floats off a 16-byte boundary."""
+    x = np.ascontiguousarray(x)
+    buf = torch.empty(x.size + 4, device="cuda", dtype=torch.from_numpy(x).dtype)
+    t = buf[shift:shift + x.size].view(*x.shape)
+    t.copy_(torch.from_numpy(x))
+    return t
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def rownorm_err(got, ref):
+    den = np.abs(ref).max(axis=1)
+    num = np.abs(got.astype(np.float64) - ref).max(axis=1)
+    return float(np.max(np.where(den > 0, num / np.where(den > 0, den, 1), num)))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (127, 256, 129), (128, 255, 130), (129, 33, 131), (257, 130, 383)])
+@pytest.mark.parametrize("qb_x,qb_w", [(("ptq", 8, 0), ("ptq", 8, 0)), (("psq", 4, 0), ("shift", 4, 0)),
+                                       (("bhq", 5, 64), ("ptq", 8, 0)), (("bhq", 5, 48), ("shift", 6, 0))])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_linear_padded(shape, qb_x, qb_w, shift):
+    N, d_in, d_out = shape
+    X, W, G = synth.linear_small(seed=sum(shape), n=N, d_in=d_in, d_out=d_out)
+    r = BW.linear_backward(X, W, G, qb_x=qb_x, qb_w=qb_w, seed=9)
+    f = fqt()
+    gW, gX, ws = f.fqt_linear_backward(dev(X, shift), dev(W, shift), dev(G, shift), qb_x=qb_x, qb_w=qb_w, seed=9)
+    assert f.fqt_workspace_status(ws) == 0
+    assert rownorm_err(host(gW), r["grad_W64"]) <= REL_TOL
+    assert rownorm_err(host(gX), r["grad_X64"]) <= REL_TOL
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 127, 65), (130, 129, 257), (65, 383, 128)])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_forward_padded(shape, shift):
+    N, d_in, d_out = shape
+    X, W, _ = synth.linear_small(seed=sum(shape), n=N, d_in=d_in, d_out=d_out)
+    f = fqt()
+    Y, ws = f.fqt_linear_forward(dev(X, shift), dev(W, shift), relu=True)
+    assert f.fqt_workspace_status(ws) == 0
+    assert rownorm_err(host(Y), CH.layer_forward(X, W, True)[1]) <= REL_TOL
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (65, 257), (64, 255), (70, 514)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_codes_of_unaligned_rows(rows, cols, shift):
+    # every offset of a row's first element in its Philox block
+    rng = np.random.default_rng(rows + cols)
+    x = (rng.standard_normal((rows, cols)) * rng.lognormal(0, 2, (rows, 1))).astype(np.float32)
+    f = fqt()
+    out = f.fqt_quantize_psq(dev(x, shift), 5, seed=3, code_sum=True)
+    ref = Q.quantize_psq(x, 5, seed=3, stream=0)
+    codes = (ref["code"] - Q.offset(5)).astype(np.int8)
+    np.testing.assert_array_equal(host(out["q"]), codes)
+    np.testing.assert_array_equal(host(out["code_sum"]), codes.astype(np.int32).sum(axis=1))
