@@ -53,45 +53,75 @@ AppdWs appd_carve(void* ws, int64_t rows) {
 }
 
 // ---------------------------------------------------------------------------
-// prep: sorted-position scalars (one thread per position)
+// prep: sorted-position scalars (one thread per position); the block after
+// them (App. D only) forms the prefix sums of M at the same time.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void appd_prep_kernel(const float* rmin, const float* rmax, int64_t rows, AppdWs w) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  const int32_t row = w.sigma[r];
+__device__ __forceinline__ void appd_norms(const float* rmin, const float* rmax, int32_t row, float& M, float& R) {
   const float lo = rmin[row], hi = rmax[row];
-  float M = fmaxf(fabsf(lo), fabsf(hi));
-  float R = hi - lo;
+  M = fmaxf(fabsf(lo), fabsf(hi));
+  R = hi - lo;
   if (!isfinite(M)) M = 0.0f;
   if (!isfinite(R)) R = 0.0f;
+}
+
+// P[i] = P[i - 1] + M_(i), one addition at a time in sorted order: a serial
+// chain of rows float64 additions.  The block stages a chunk of M in LDS (all
+// loads in flight), one thread runs the chain on 16 values at a time from and
+// to LDS, and the block stores the chunk's sums.  With the chain's loads and
+// stores in global memory 2048 rows took 52.9 us.
+constexpr int APPD_CH = 2048;
+__device__ void appd_prefix(const float* rmin, const float* rmax, int64_t rows, const AppdWs& w) {
+  __shared__ __attribute__((aligned(16))) float sm[APPD_CH];
+  __shared__ __attribute__((aligned(16))) double sp[APPD_CH];
+  const int t = threadIdx.x;
+  double P = 0.0;
+  if (t == 0) w.P[0] = 0.0;
+  for (int64_t c0 = 0; c0 < rows; c0 += APPD_CH) {
+    const int n = (int)(rows - c0 < APPD_CH ? rows - c0 : APPD_CH);
+#pragma unroll
+    for (int u = 0; u < APPD_CH / 256; ++u) {
+      const int i = t + 256 * u;
+      float M, R;
+      appd_norms(rmin, rmax, w.sigma[c0 + (i < n ? i : n - 1)], M, R);
+      sm[i] = i < n ? M : 0.0f;
+    }
+    __syncthreads();
+    if (t == 0) {
+      // positions past n add zero, and are not stored
+      for (int i = 0; i < n; i += 16) {
+        float m[16];
+        double q[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) m[u] = sm[i + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          P = P + (double)m[u];
+          q[u] = P;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sp[i + u] = q[u];
+      }
+    }
+    __syncthreads();
+    for (int i = t; i < n; i += 256) w.P[c0 + i + 1] = sp[i];
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void appd_prep_kernel(const float* rmin, const float* rmax, int64_t rows, AppdWs w,
+                                                        int64_t nprep) {
+  if ((int64_t)blockIdx.x >= nprep) {
+    appd_prefix(rmin, rmax, rows, w);
+    return;
+  }
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= rows) return;
+  float M, R;
+  appd_norms(rmin, rmax, w.sigma[r], M, R);
   w.Ms[r] = M;
   w.Rs[r] = R;
   w.ca[r] = cbrt_rn(R);
   w.cc[r] = cbrt_rn(2.0f * M);
-}
-
-// P[i] = P[i - 1] + M_(i), one addition at a time in sorted order (one
-// thread; the loads of a batch are issued before its additions).
-__global__ __launch_bounds__(64) void appd_prefix_kernel(int64_t rows, AppdWs w) {
-  if (threadIdx.x != 0) return;
-  double P = 0.0;
-  w.P[0] = 0.0;
-  int64_t i = 0;
-  constexpr int U = 16;
-  for (; i + U <= rows; i += U) {
-    float m[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) m[u] = w.Ms[i + u];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      P = P + (double)m[u];
-      w.P[i + u + 1] = P;
-    }
-  }
-  for (; i < rows; ++i) {
-    P = P + (double)w.Ms[i];
-    w.P[i + 1] = P;
-  }
 }
 
 // First j groups' share of the small rows for G groups (App. D, step 2):
@@ -123,10 +153,15 @@ __device__ __forceinline__ double appd_term(const AppdWs& w, int64_t G, int64_t 
 
 // One wave per G (four per block, the largest G first): 64 groups' terms
 // at a time in parallel, then added to the total one at a time in group
-// order (float64).
+// order (float64).  The terms meet in LDS, where every lane reads them as
+// broadcasts and runs the same chain of additions: the chain, not the term
+// arithmetic, bounds the kernel (2048 rows: 145 us with one cross-lane
+// permute per term).  Terms past G are zero, and adding +0 to a total that is
+// never -0 changes nothing.
 __global__ __launch_bounds__(256) void appd_objective_kernel(int64_t rows, int B, AppdWs w, double* obj) {
-  const int lane = threadIdx.x & 63;
-  const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  __shared__ __attribute__((aligned(16))) double sterm[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t id = (int64_t)blockIdx.x * 4 + wave;
   if (id >= rows) return;
   const int64_t G = rows - id;
   double total = 0.0;
@@ -134,10 +169,11 @@ __global__ __launch_bounds__(256) void appd_objective_kernel(int64_t rows, int B
     const int64_t i = i0 + lane;
     double t = 0.0;
     if (i < G) t = appd_term(w, G, i, appd_cum(w.P, rows, G, i), appd_cum(w.P, rows, G, i + 1), B);
-    const int nl = (int)(G - i0 < 64 ? G - i0 : 64);
-    for (int l = 0; l < nl; ++l) {
-      total = total + __shfl(t, l, 64);
-    }
+    sterm[wave][lane] = t;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int l = 0; l < 64; ++l) total = total + sterm[wave][l];
+    __builtin_amdgcn_wave_barrier();
   }
   if (lane == 0) obj[G - 1] = total;
 }
@@ -231,19 +267,21 @@ __global__ __launch_bounds__(256) void plan_build_kernel(const float* rmin, int6
   }
 }
 
-static hipError_t launch_prep(const float* rmin, const float* rmax, int64_t rows, const AppdWs& w, hipStream_t s) {
-  hipLaunchKernelGGL(appd_prep_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, rmin, rmax, rows, w);
+static hipError_t launch_prep(const float* rmin, const float* rmax, int64_t rows, const AppdWs& w, bool prefix,
+                              hipStream_t s) {
+  const int64_t nprep = (rows + 255) / 256;
+  hipLaunchKernelGGL(appd_prep_kernel, dim3((unsigned)(nprep + (prefix ? 1 : 0))), dim3(256), 0, s, rmin, rmax, rows, w,
+                     nprep);
   return hipGetLastError();
 }
 
 hipError_t launch_appd_search(const float* rmin, const float* rmax, int64_t rows, int bits, const AppdWs& w,
                               double* obj_out, int32_t* num_groups, hipStream_t s) {
   if (rows < 1 || rows > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipError_t e = launch_prep(rmin, rmax, rows, w, s);
+  hipError_t e = launch_prep(rmin, rmax, rows, w, true, s);
   if (e != hipSuccess) return e;
   const int B = (1 << bits) - 1;
   double* obj = obj_out ? obj_out : w.obj;
-  hipLaunchKernelGGL(appd_prefix_kernel, dim3(1), dim3(64), 0, s, rows, w);
   hipLaunchKernelGGL(appd_objective_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, rows, B, w, obj);
   hipLaunchKernelGGL(appd_argmin_kernel, dim3(1), dim3(1024), 0, s, rows, obj, num_groups ? num_groups : w.G);
   return hipGetLastError();
@@ -257,7 +295,7 @@ hipError_t launch_general_plan(const float* rmin, const float* rmax, int64_t row
   if (block_size == 0) {
     e = launch_appd_search(rmin, rmax, rows, bits, w, obj_out, w.G, s);
   } else {
-    e = launch_prep(rmin, rmax, rows, w, s);
+    e = launch_prep(rmin, rmax, rows, w, false, s);
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(plan_build_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, rmin, rows,
@@ -266,83 +304,190 @@ hipError_t launch_general_plan(const float* rmin, const float* rmax, int64_t row
 }
 
 // ---------------------------------------------------------------------------
-// tau: block (column tile of 256, chunk of 64 slots); the groups whose first
-// slot lies in the chunk, one column per thread, their rows one at a time
-// in slot order (each batch's loads issued before its additions).
+// tau and inverse share their split: a block takes 64 columns (one per lane)
+// and the multi-row groups whose first slot lies in its chunk of 64 slots.
+// Groups of at most GW_ROWS rows go to one wave each; the rows of a larger
+// group are spread over the block's waves.  With one thread per column
+// walking every row of its chunk's groups, an adaptive plan of 2048 x 1024
+// (128 blocks, groups of hundreds of rows) took 33 us (tau) and 76 us
+// (inverse).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bhq_tau_kernel(const float* x, int64_t rows, int64_t cols, const int32_t* perm,
-                                                      const float* scale, const SlotInfo* slot, float* tau) {
-  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.y * 64;
-  const int64_t s1 = s0 + 64 < rows ? s0 + 64 : rows;
+constexpr int GW_WAVES = 8;
+constexpr int GW_ROWS = 64;
+
+// Bit b: a group of at least two rows starts at slot s0 + b of the chunk;
+// size: the lane's slot record (lane b holds slot s0 + b).
+__device__ __forceinline__ uint64_t chunk_groups(const SlotInfo* slot, int64_t s0, int64_t rows, SlotInfo& si) {
+  const int lane = threadIdx.x & 63;
+  const int64_t sb = s0 + lane;
+  si = slot[sb < rows ? sb : rows - 1];
+  return __ballot(sb < rows && si.base == sb && si.size >= 2);
+}
+
+// A group's column sum S of v_p = d_p x[perm[p]] adds its rows one at a time
+// in slot order (float32); in a large group the waves load and scale 64 rows
+// at a time into LDS, from where the first wave adds them in order.
+__global__ __launch_bounds__(64 * GW_WAVES) void bhq_tau_kernel(const float* x, int64_t rows, int64_t cols,
+                                                                const int32_t* perm, const float* scale,
+                                                                const SlotInfo* slot, float* tau) {
+  __shared__ float sv[2][64][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t col = (int64_t)blockIdx.x * 64 + lane;
   const int64_t cc = col < cols ? col : cols - 1;  // clamped: loads stay inside x, the store is skipped
-  for (int64_t sb = s0; sb < s1; ++sb) {
-    const SlotInfo si = slot[sb];
-    if (si.base != sb || si.size < 2) continue;
+  const int64_t s0 = (int64_t)blockIdx.y * 64;
+  SlotInfo lsi;
+  const uint64_t groups = chunk_groups(slot, s0, rows, lsi);
+  int k = 0;
+  for (uint64_t m = groups; m; m &= m - 1) {
+    const int b = __ffsll((unsigned long long)m) - 1;
+    const int size = __builtin_amdgcn_readlane(lsi.size, b);
+    const float alpha = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lsi.alpha), b));
+    const float oma = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lsi.oma), b));
+    const int64_t sb = s0 + b;
     float S = 0.0f, v0 = 0.0f;
-    int64_t p = 0;
-    constexpr int U = 8;
-    for (; p + U <= si.size; p += U) {
-      float v[U];
+    if (size <= GW_ROWS) {
+      if (k++ % GW_WAVES != wave) continue;
+      // the group's rows and scales, lane p holding slot p; eight loads in flight
+      const int64_t sp = sb + (lane < size ? lane : 0);
+      const int32_t lrow = perm[sp];
+      const float ld = scale[sp];
+      constexpr int U = 8;
+      for (int p = 0; p < size; p += U) {
+        float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = scale[sb + p + u] * x[(int64_t)perm[sb + p + u] * cols + cc];
-      if (p == 0) v0 = v[0];
+        for (int u = 0; u < U; ++u) {
+          const int q = p + u < size ? p + u : size - 1;
+          const float d = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ld), q));
+          v[u] = d * x[(int64_t)__builtin_amdgcn_readlane(lrow, q) * cols + cc];
+        }
+        if (p == 0) v0 = v[0];
 #pragma unroll
-      for (int u = 0; u < U; ++u) S = S + v[u];
+        for (int u = 0; u < U; ++u)
+          if (p + u < size) S = S + v[u];
+      }
+    } else {
+      const int nch = (size + 63) / 64;
+      auto fill = [&](int c) {
+        constexpr int RW = 64 / GW_WAVES;  // rows per wave
+        const int64_t base = sb + 64 * (int64_t)c + wave * RW;
+        const int left = size - 64 * c - wave * RW;  // rows of this wave in the chunk (may be <= 0)
+        const int64_t sp = base + ((lane & (RW - 1)) < left ? (lane & (RW - 1)) : 0);
+        const int64_t sq = sp < sb + size ? sp : sb;
+        const int32_t lrow = perm[sq];
+        const float ld = scale[sq];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+          const float d = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ld), r));
+          sv[c & 1][wave * RW + r][lane] = d * x[(int64_t)__builtin_amdgcn_readlane(lrow, r) * cols + cc];
+        }
+      };
+      fill(0);
+      for (int c = 0; c < nch; ++c) {
+        __syncthreads();  // chunk c is in LDS, and chunk c - 1 has been added
+        if (c + 1 < nch) fill(c + 1);
+        if (wave == 0) {
+          const int n = size - 64 * c < 64 ? size - 64 * c : 64;
+          if (c == 0) v0 = sv[0][0][lane];
+          if (n == 64) {
+#pragma unroll
+            for (int r = 0; r < 64; ++r) S = S + sv[c & 1][r][lane];
+          } else {
+            for (int r = 0; r < n; ++r) S = S + sv[c & 1][r][lane];
+          }
+        }
+      }
+      __syncthreads();  // the next group's first fill reuses the buffers
+      if (wave != 0) continue;
     }
-    for (; p < si.size; ++p) {
-      const float v = scale[sb + p] * x[(int64_t)perm[sb + p] * cols + cc];
-      if (p == 0) v0 = v;
-      S = S + v;
-    }
-    const float m = si.alpha * S - v0;
-    if (col < cols) tau[(sb >> 1) * cols + col] = __fdiv_rn(m, si.oma);
+    const float mm = alpha * S - v0;
+    if (col < cols) tau[(sb >> 1) * cols + col] = __fdiv_rn(mm, oma);
   }
 }
 
 hipError_t launch_bhq_tau(const float* x, int64_t rows, int64_t cols, const int32_t* perm, const float* scale,
                           const SlotInfo* slot, float* tau, hipStream_t s) {
-  const int64_t cb = (cols + 255) / 256, rb = (rows + 63) / 64;
+  const int64_t cb = (cols + 63) / 64, rb = (rows + 63) / 64;
   if (cb > 0x7FFFFFFF || rb > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bhq_tau_kernel, dim3((unsigned)cb, (unsigned)rb), dim3(256), 0, s, x, rows, cols, perm, scale,
+  hipLaunchKernelGGL(bhq_tau_kernel, dim3((unsigned)cb, (unsigned)rb), dim3(64 * GW_WAVES), 0, s, x, rows, cols, perm, scale,
                      slot, tau);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// inverse: block (column tile of 256, chunk of 64 slots, row block b); the
-// multi-row groups whose first slot lies in the chunk
+// inverse: the split of bhq_tau_kernel, for row block b.  S adds the rows of
+// a large group wave by wave (float64), each wave's rows in slot order.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bhq_inverse_kernel(InverseParams p) {
-  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(64 * GW_WAVES) void bhq_inverse_kernel(InverseParams p) {
+  __shared__ double ss[GW_WAVES][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t col = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t cc = col < p.cols ? col : p.cols - 1;
   const int64_t s0 = (int64_t)blockIdx.y * 64;
-  const int64_t s1 = s0 + 64 < p.rows ? s0 + 64 : p.rows;
   const int64_t b = blockIdx.z;
-  if (col >= p.cols) return;
-  const double* T = p.T + (b * p.tstride) * p.ldt + col;
-  for (int64_t sb = s0; sb < s1; ++sb) {
-    const SlotInfo si = p.slot[sb];
-    if (si.base != sb || si.size < 2) continue;
+  const double* T = p.T + (b * p.tstride) * p.ldt + cc;
+  SlotInfo lsi;
+  const uint64_t groups = chunk_groups(p.slot, s0, p.rows, lsi);
+  int k = 0;
+  for (uint64_t m = groups; m; m &= m - 1) {
+    const int bit = __ffsll((unsigned long long)m) - 1;
+    const int size = __builtin_amdgcn_readlane(lsi.size, bit);
+    const int64_t sb = s0 + bit;
+    const bool one = size <= GW_ROWS;  // one wave's group, else the block's
+    if (one && k++ % GW_WAVES != wave) continue;
+    const int w0 = one ? 0 : wave, step = one ? 1 : GW_WAVES;
+    constexpr int U = 8;
     double S = 0.0;
-    for (int64_t q = 0; q < si.size; ++q) S = S + T[(sb + q) * p.ldt];
+    for (int q = w0; q < size; q += U * step) {
+      double v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = q + u * step;
+        v[u] = T[(sb + (r < size ? r : 0)) * p.ldt];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) S = S + (q + u * step < size ? v[u] : 0.0);
+    }
+    if (!one) {
+      __syncthreads();  // the sums of the previous group have been read
+      ss[wave][lane] = S;
+      __syncthreads();
+      S = 0.0;
+#pragma unroll
+      for (int w = 0; w < GW_WAVES; ++w) S = S + ss[w][lane];
+    }
     const double T0 = T[sb * p.ldt];
-    const double alpha = 1.0 / sqrt((double)si.size);
+    const double alpha = 1.0 / sqrt((double)size);
     const double tau = (alpha * S - T0) / (1.0 - alpha);
     const double up0 = (1.0 - alpha) * tau, dn = alpha * tau;
-    for (int64_t q = 0; q < si.size; ++q) {
-      const double t = T[(sb + q) * p.ldt];
-      const double v = (q == 0 ? t + up0 : t - dn) / (double)p.scale[sb + q];
-      const int64_t o = ((int64_t)p.perm[sb + q] * p.ostride + b * p.obstride) * p.ldo + col;
-      const float f = (float)v;
-      p.out[o] = (p.mask && !(p.mask[o] > 0.0f)) ? 0.0f : f;
+    for (int q = w0; q < size; q += U * step) {
+      double v[U];
+      float d[U];
+      int32_t row[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t r = sb + (q + u * step < size ? q + u * step : 0);
+        v[u] = T[r * p.ldt];
+        d[u] = p.scale[r];
+        row[u] = p.perm[r];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = q + u * step;
+        if (r >= size || col >= p.cols) continue;
+        const float f = (float)((r == 0 ? v[u] + up0 : v[u] - dn) / (double)d[u]);
+        const int64_t o = ((int64_t)row[u] * p.ostride + b * p.obstride) * p.ldo + col;
+        p.out[o] = (p.mask && !(p.mask[o] > 0.0f)) ? 0.0f : f;
+      }
     }
   }
 }
 
 hipError_t launch_bhq_inverse(const InverseParams& p, hipStream_t s) {
-  const int64_t cb = (p.cols + 255) / 256, rb = (p.rows + 63) / 64;
+  const int64_t cb = (p.cols + 63) / 64, rb = (p.rows + 63) / 64;
   if (cb > 0x7FFFFFFF || rb > 65535 || p.nblk > 65535 || p.nblk < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bhq_inverse_kernel, dim3((unsigned)cb, (unsigned)rb, (unsigned)p.nblk), dim3(256), 0, s, p);
+  hipLaunchKernelGGL(bhq_inverse_kernel, dim3((unsigned)cb, (unsigned)rb, (unsigned)p.nblk), dim3(64 * GW_WAVES), 0, s, p);
   return hipGetLastError();
 }
 
