@@ -415,36 +415,23 @@ fqt_status check_conv_shape(const fqt_conv_shape& sh) {
   return FQT_OK;
 }
 
+// X codes: at most 4 channels are packed to one word per pixel, four kernel
+// columns to a 16-byte chunk of the grad_W contraction (a 7 x 7 stem on 3
+// channels then has 224 columns instead of 784); image rows get a zero halo
+// wide enough for the last chunk.
 ConvGeom conv_geom(const fqt_conv_shape& sh) {
-  ConvGeom g{sh.n, sh.c, sh.h, sh.w, sh.o, sh.kh, sh.kw, sh.stride, sh.pad, sh.ho, sh.wo, 0, 0, 0, 0, 0};
+  ConvGeom g{sh.n, sh.c, sh.h, sh.w, sh.o, sh.kh, sh.kw, sh.stride, sh.pad, sh.ho, sh.wo, 0, 0, 0};
   g.npad = ((int64_t)sh.n + 63) / 64 * 64;
-  g.psp = (int64_t)sh.ho * sh.wo;
-  return g;
-}
-
-// The grad_W layout.  Stride 1: the implicit form on the zero-halo grid
-// (rows of gwp = w + 2 pad rounded up to 16 bytes) when a slot's grid pitch
-// is at most 1.5 times its output pixels (rounded up to 128 for a per-sample
-// Q_b1), else the explicit im2col.  Per-sample Q_b1: each slot's pixels start
-// a 128-byte K stage.
-ConvGeom conv_geom(const fqt_conv_shape& sh, const fqt_bwd_cfg& cfg) {
-  ConvGeom g = conv_geom(sh);
-  const bool psq1 = cfg.qb_w.kind == FQT_PSQ;
-  const int64_t howo = g.psp;
-  const int64_t compact = psq1 ? (howo + 127) / 128 * 128 : howo;
-  if (sh.stride == 1) {
-    const int64_t gwp = ((int64_t)sh.w + 2 * sh.pad + 15) / 16 * 16, ghp = (int64_t)sh.h + 2 * sh.pad;
-    const int64_t gsp = (ghp * gwp + 127) / 128 * 128;
-    if (2 * gsp <= 3 * compact && gwp <= 4096 && (!psq1 || gsp <= MAX_K_CHUNK)) {
-      g.gwp = gwp;
-      g.ghp = ghp;
-      g.psp = gsp;
-      // copies reach r gwp <= (kh - 1) gwp past the last slot's K range
-      g.ldx = ((int64_t)sh.n * gsp + (sh.kh - 1) * gwp + 127) / 128 * 128;
-      return g;
+  g.cp = (sh.c + 15) / 16 * 16;
+  if (sh.c <= 4) {
+    const int64_t full = (int64_t)sh.w + 2 * (int64_t)sh.pad;
+    const int64_t reach = (int64_t)(sh.wo - 1) * sh.stride + ((int64_t)sh.kw + 3) / 4 * 4;
+    const int64_t wp = ((full > reach ? full : reach) + 3) / 4 * 4;
+    if ((int64_t)sh.n * sh.h * wp < ((int64_t)1 << 31)) {
+      g.cp = 4;
+      g.wp = (int)wp;
     }
   }
-  g.psp = compact;
   return g;
 }
 
@@ -452,16 +439,16 @@ struct ConvWs {
   Header h;
   StatsSeg sx_seg, sw_seg, sg_seg;
   float *rmin, *rmax;
-  int8_t *xq_t, *wq_t, *q2, *q1_t, *bw;
-  int32_t *swq, *sumB, *xs, *qs, *sumA_tap, *count_tap, *sg, *rs, *ct, *cnt;
+  int8_t *xq, *wq_t, *q2, *q1;
+  int32_t *swq, *sg, *rs, *ct, *cnt;
+  int32_t* counters;  // cleared before the quantizers: gw.sumB, gw.qs
+  int64_t ncounters;
+  int64_t xbytes;
   float *sx, *zx, *sw, *zw, *sg1, *zg1, *sg2, *zg2;
   int32_t* perm;
   BhqWs bhq;
   double* tbuf;      // general BHQ plan: T rows (input pixel, slot) of multi-row groups [h w npad, c]
-  ConvPsqSums ps;    // per-sample Q_b1
-  int32_t* part;
-  int64_t ldq, kchunk;
-  int splits;
+  ConvGradwParams gw;
 };
 
 ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, const ConvGeom& g,
@@ -469,7 +456,6 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   ConvWs w{};
   const int64_t N = g.n, hw = (int64_t)g.h * g.w, howo = (int64_t)g.ho * g.wo;
   const int64_t taps = (int64_t)g.kh * g.kw;
-  const int64_t P = N * howo;
   w.h = take_header(c);
   w.sx_seg = stats_flat_seg(X, N * hw * g.c);
   w.sw_seg = stats_flat_seg(W, (int64_t)g.o * taps * g.c);
@@ -481,19 +467,12 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   w.rmax = c.take<float>(N);
   stats_direct_rows(w.sg_seg, w.rmin, w.rmax);
   const bool psq1 = cfg.qb_w.kind == FQT_PSQ;
-  w.ldq = (psq1 || g.gwp > 0) ? N * g.psp : (P + 127) / 128 * 128;
-  w.xq_t = c.take<int8_t>((int64_t)g.c * N * hw);
+  w.xbytes = g.cp == 4 ? N * g.h * g.wp * 4 : N * hw * g.cp;
+  w.xq = c.take<int8_t>(w.xbytes);
   w.wq_t = c.take<int8_t>((int64_t)g.c * taps * g.o);
   w.q2 = c.take<int8_t>(N * howo * g.o);
-  w.q1_t = c.take<int8_t>((int64_t)g.o * w.ldq);
-  // explicit im2col [(tap, c)][ldq], or the kw shifted activation grids [s][c][ldx]
-  w.bw = c.take<int8_t>(g.gwp > 0 ? (int64_t)g.kw * g.c * g.ldx : taps * g.c * w.ldq);
+  w.q1 = c.take<int8_t>(N * howo * g.o);
   w.swq = c.take<int32_t>(taps * g.c);
-  w.sumB = c.take<int32_t>(taps * g.c);
-  w.xs = c.take<int32_t>((int64_t)g.c * g.h * g.w);
-  w.qs = c.take<int32_t>((int64_t)g.o * howo);
-  w.sumA_tap = c.take<int32_t>((int64_t)g.o * taps);
-  w.count_tap = c.take<int32_t>(taps);
   w.sg = c.take<int32_t>(N * howo);
   w.rs = c.take<int32_t>(N * hw);
   w.ct = c.take<int32_t>(hw * g.c);
@@ -511,42 +490,27 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
     w.bhq = carve_bhq(c, N, howo * g.o, cfg.qb_x.block_size);
     if (w.bhq.general) w.tbuf = c.take<double>(hw * g.npad * g.c);
   }
+  // grad_W
+  ConvGradwParams& p = w.gw;
+  p.q1 = w.q1;
+  p.xq = w.xq;
+  p.Np = conv_gradw_cols(g);
+  conv_gradw_splits(g, psq1, p.per_split, p.splits);
+  const int64_t parts = (int64_t)p.splits * g.o * p.Np;
   if (psq1) {
-    // one K block per slot: exact int32 partials, weighted in float64
-    w.ps.dA = c.take<double>(N);
-    w.ps.zA = c.take<double>(N);
-    w.ps.zsum = c.take<double>(1);
-    w.ps.qw = c.take<double>((int64_t)g.o * howo);
-    w.ps.xw = c.take<double>((int64_t)g.c * hw);
-    w.ps.WA = c.take<double>((int64_t)g.o * taps);
-    w.ps.WB = c.take<double>(taps * g.c);
-    w.kchunk = g.psp;
-    w.splits = (int)N;
-    w.part = c.take<int32_t>(N * g.o * taps * g.c);
-    return w;
+    p.partd = c.take<double>(parts);
+    p.sumBd = c.take<double>((int64_t)p.splits * 2 * p.Np);
+    p.qsd = c.take<double>(howo * g.o);
+    p.sumAd = c.take<double>(taps * g.o);
+    p.zsum = c.take<double>(1);
+  } else {
+    p.part = c.take<int32_t>(parts);
+    w.ncounters = p.Np + howo * g.o;
+    w.counters = c.take<int32_t>(w.ncounters);
+    p.sumB = w.counters;
+    p.qs = w.counters ? w.counters + p.Np : nullptr;
+    p.sumA = c.take<int32_t>(taps * g.o);
   }
-  // grad_W: split the pixel contraction so that at most 512 blocks run (two
-  // full rounds of one block per CU), in a multiple of the XCD count of
-  // splits when there are that many, each K chunk a whole number of 128-byte
-  // stages and at most 65536
-  const int64_t tiles = (g.o <= 64 ? 1 : (g.o + 127) / 128) * ((taps * g.c + 127) / 128);
-  int64_t want = 512 / tiles;
-  if (want >= NUM_XCD) want = want / NUM_XCD * NUM_XCD;
-  const int64_t stages = w.ldq / 128;
-  if (want > stages) want = stages;
-  if (want < 1) want = 1;
-  int64_t kchunk = (stages + want - 1) / want * 128;
-  if (kchunk > 65536) kchunk = 65536;
-  int64_t splits = (w.ldq + kchunk - 1) / kchunk;
-  if (splits >= NUM_XCD && splits % NUM_XCD != 0) {
-    // a multiple of the XCD count, so that the contraction keeps each
-    // split's tiles on one XCD (trailing splits may be empty: zero partials)
-    splits = (splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-    kchunk = (stages + splits - 1) / splits * 128;
-  }
-  w.kchunk = kchunk;
-  w.splits = (int)splits;
-  w.part = c.take<int32_t>((int64_t)w.splits * g.o * taps * g.c);
   return w;
 }
 
@@ -1139,7 +1103,7 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
   }
   if (!ws) return FQT_EWORKSPACE;
   if (ws_bytes < fqt_conv_backward_workspace(shape, cfg)) return FQT_EWORKSPACE;
-  const ConvGeom g = conv_geom(*shape, *cfg);
+  const ConvGeom g = conv_geom(*shape);
   const bool psq1 = cfg->qb_w.kind == FQT_PSQ;
   Carver c(ws);
   ConvWs w = carve_conv(c, X, W, G, g, *cfg);
@@ -1149,7 +1113,7 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
   int32_t* const perm = bhq ? w.perm : nullptr;
   const Tracer tr{cfg->trace, s};
   const int64_t N = g.n, D = (int64_t)g.ho * g.wo * g.o;
-  const int64_t hw = (int64_t)g.h * g.w, howo = (int64_t)g.ho * g.wo;
+  const int64_t hw = (int64_t)g.h * g.w;
   const int64_t taps = (int64_t)g.kh * g.kw;
 
   tr.begin(0);
@@ -1160,6 +1124,8 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
   sp.seg[1] = w.sw_seg;
   sp.seg[2] = w.sg_seg;
   sp.nseg = 3;
+  sp.zero = w.counters;
+  sp.zero_n = w.ncounters;
   FQT_TRY(launch_stats(sp, s));
   tr.end(1);
   tr.begin(2);
@@ -1177,7 +1143,6 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
   fp.out[2] = ScaleOut{2, cfg->qb_w.bits, psq1 ? 1 : 0, w.sg1, w.zg1};
   fp.nout = 3;
   if (!bhq && want_x) fp.out[fp.nout++] = ScaleOut{2, qx.bits, qx.kind == FQT_PSQ ? 1 : 0, w.sg2, w.zg2};
-  if (!psq1) add_zero(fp, w.sumB, taps * g.c);
   if (bhq) add_zero(fp, bhq_plan_carve(w.bhq.plan, N).rank, N);
   const bool fin_in_plan = bhq && w.sg_seg.rmin != nullptr;
   if (!fin_in_plan) FQT_TRY(launch_finalize(fp, s));
@@ -1190,108 +1155,68 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
   }
   tr.end(2);
 
-  // Q_f(X): codes [c][pixels], samples in slot order
+  // one launch (phase 5; phases 3 and 4 stay empty): Q_b2(G) [(y, x)][slot][o]
+  // (stream 1) and Q_b1(G) [n][(y, x)][o] (stream 0) from one read of G, Q_f(X)
+  // in pixel order, Q_theta(W) [c][(r, s, o)] with its sums over o
   tr.begin(3);
-  NarrowQParams nx{};
-  nx.x = X;
-  nx.rows = N * hw;
-  nx.cols = g.c;
-  nx.perm = perm;
-  nx.blk = hw;
-  nx.bits = cfg->f_bits;
-  nx.scale = w.sx;
-  nx.zero = w.zx;
-  nx.q_t = w.xq_t;
-  nx.ldt = N * hw;
-  FQT_TRY(launch_quant_narrow_t(nx, s));
   tr.end(3);
-  // Q_theta(W): codes [c][(r, s, o)] and their sums over o
   tr.begin(4);
-  if (want_x) FQT_TRY(launch_conv_wq(W, g, cfg->theta_bits, w.sw, w.zw, w.wq_t, w.swq, s));
   tr.end(4);
-  // Q_b2(G) [slot][(y, x, o)] (stream 1); Q_b1(G) [o][pixels] (stream 0)
   tr.begin(5);
+  PixelQParams px{};
+  px.x = X;
+  px.words = w.xbytes / 4;
+  px.c = g.c;
+  px.cp = g.cp;
+  px.w = g.w;
+  px.wp = g.wp;
+  px.pad = g.pad;
+  px.bits = cfg->f_bits;
+  px.scale = w.sx;
+  px.zero = w.zx;
+  px.q = w.xq;
+  ConvWQParams pw{};
+  if (want_x) pw = ConvWQParams{W, g.o, (int)taps, g.c, cfg->theta_bits, w.sw, w.zw, w.wq_t, w.swq};
   QuantParams pg{};
   pg.x = G;
   pg.rows = N;
   pg.cols = D;
-  pg.perm = w.perm;
+  pg.perm = perm;
   pg.bits = qx.bits;
   pg.stoch = 1;
   pg.seed = cfg->seed;
   pg.stream = 1;
   pg.scale = w.sg2;
   pg.zero = w.zg2;
-  pg.q_nat = w.q2;
-  pg.pm_o = g.o;  // [output pixel][slot][o]: a grad_X tile's slots of one tap read one contiguous run
+  pg.q_nat = want_x ? w.q2 : nullptr;
+  pg.pm_o = want_x ? g.o : 0;  // a grad_X tile's slots of one tap read one contiguous run
+  pg.bits2 = cfg->qb_w.bits;
+  pg.stream2 = 0;
+  pg.scale2 = w.sg1;
+  pg.zero2 = w.zg1;
+  pg.row2 = psq1 ? 1 : 0;
+  pg.q2_n = w.q1;
+  pg.sum2_t = w.gw.qs;
   if (bhq) {
     st = bhq_params(w.bhq, G, N, D, qx.block_size, w.perm, w.sg2, pg, s);
     if (st != FQT_OK) return st;
   }
-  if (want_x) FQT_TRY(launch_quant(pg, mode, s));
-  NarrowQParams n1{};
-  n1.x = G;
-  n1.rows = N * g.psp;
-  n1.cols = g.o;
-  n1.perm = perm;
-  n1.blk = g.psp;
-  n1.vblk = howo;
-  n1.rowscale = psq1 ? 1 : 0;
-  if (g.gwp > 0) {  // output pixel (y, x) at y gwp + x of its slot's grid
-    n1.gw = g.gwp;
-    n1.gwo = g.wo;
-    n1.gho = g.ho;
-  }
-  n1.bits = cfg->qb_w.bits;
-  n1.stoch = 1;
-  n1.seed = cfg->seed;
-  n1.stream = 0;
-  n1.scale = w.sg1;
-  n1.zero = w.zg1;
-  n1.q_t = w.q1_t;
-  n1.ldt = w.ldq;
-  FQT_TRY(launch_quant_narrow_t(n1, s));
+  FQT_TRY(launch_quant_conv(pg, mode, px, pw, s));
   tr.end(5);
 
   // grad_W [o][(r, s, c)] = Q_b1(G)^T im2col(Q_f(X)), split over output pixels
   tr.begin(6);
-  FQT_TRY(launch_conv_im2col_w(g, w.xq_t, w.bw, g.gwp > 0 ? g.ldx : w.ldq, psq1 ? nullptr : w.xs, w.sumB, s));
-  if (psq1)
-    FQT_TRY(launch_conv_psq_sums(g, w.sg1, w.zg1, perm, 1 << (cfg->qb_w.bits - 1), w.q1_t, w.ldq, w.xq_t, w.ps,
-                                 w.count_tap, s));
-  else
-    FQT_TRY(launch_conv_tapsums(g, w.q1_t, w.ldq, w.qs, w.sumA_tap, w.count_tap, s));
-  GemmParams gw{};
-  gw.A = w.q1_t;
-  gw.B = w.bw;
-  gw.M = g.o;
-  gw.N = taps * g.c;
-  gw.K = w.ldq;
-  gw.lda = w.ldq;
-  gw.ldb = w.ldq;
-  if (g.gwp > 0) {  // tap (r, s), channel c: copy s at K offset r gwp
-    gw.ldb = g.ldx;
-    gw.bmap_c = g.c;
-    gw.bmap_kw = g.kw;
-    gw.bmap_wp = g.gwp;
-  }
-  gw.splits = w.splits;
-  gw.kchunk = w.kchunk;
-  gw.part = w.part;
-  gw.out = grad_W;
-  gw.ldo = taps * g.c;
-  gw.sumB = w.sumB;
+  ConvGradwParams gw = w.gw;
   gw.scaleA = w.sg1;
   gw.zeroA = w.zg1;
   gw.halfA = 1 << (cfg->qb_w.bits - 1);
   gw.scaleB = w.sx;
   gw.zeroB = w.zx;
   gw.halfB = 1 << (cfg->f_bits - 1);
-  FQT_TRY(launch_gemm(gw, EPI_RAW_I32, s));
-  if (psq1)
-    FQT_TRY(launch_conv_gradw_psq_reduce(gw, g, w.ps, w.count_tap, s));
-  else
-    FQT_TRY(launch_conv_gradw_reduce(gw, g, w.sumA_tap, w.count_tap, s));
+  gw.out = grad_W;
+  FQT_TRY(launch_conv_sums(gw, g, psq1, w.q2, want_x ? w.sg : nullptr, s));
+  FQT_TRY(launch_conv_gradw(gw, g, psq1, s));
+  FQT_TRY(launch_conv_gradw_reduce(gw, g, psq1, s));
   tr.end(6);
 
   // grad_X [n][h][w][c] = col2im(Q_b2(G) Q_theta(W)), implicit im2col rows
@@ -1301,7 +1226,7 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
     return FQT_OK;
   }
   tr.begin(7);
-  FQT_TRY(launch_conv_gradx_prep(g, w.q2, w.swq, w.sg, w.rs, w.ct, w.cnt, s));
+  FQT_TRY(launch_conv_gradx_prep(g, w.swq, w.sg, w.rs, w.ct, w.cnt, s));
   GemmParams gx{};
   gx.B = w.wq_t;
   gx.M = hw * g.npad;
@@ -1351,7 +1276,7 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
 size_t fqt_conv_backward_workspace(const fqt_conv_shape* shape, const fqt_bwd_cfg* cfg) {
   if (!shape || !cfg || check_conv_shape(*shape) != FQT_OK) return 0;
   Carver c(nullptr);
-  carve_conv(c, nullptr, nullptr, nullptr, conv_geom(*shape, *cfg), *cfg);
+  carve_conv(c, nullptr, nullptr, nullptr, conv_geom(*shape), *cfg);
   return c.off;
 }
 

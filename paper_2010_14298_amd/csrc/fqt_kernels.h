@@ -39,7 +39,10 @@ struct StatsPlan {
   StatsSeg seg[3];
   int nseg;
   int64_t block_start[4];
+  int32_t* zero;  // counters cleared in the same launch (zero_n of them, 0: none)
+  int64_t zero_n;
 };
+constexpr int64_t STATS_ZERO = 4096;  // counters per clearing block
 hipError_t launch_stats(StatsPlan sp, hipStream_t s);
 
 // One finalize block: per-tensor PTQ scale / zero (Sec. 3.3), per-row PSQ
@@ -198,7 +201,9 @@ struct QuantParams {
   const float* scale2;
   const float* zero2;
   int8_t* q2_t;
-  int32_t* sum2_t;
+  int8_t* q2_n;        // natural instead: [rows, cols] in source-row order (cols % 16 == 0)
+  int row2;            // q2_n: scale2 / zero2 per source row
+  int32_t* sum2_t;     // [cols] column sums, or nullptr
   const int8_t* shift;   // QM_ROW: per-row left shift of the offset codes, or nullptr
   const int8_t* shift2;  // Q_b1 with per-row scale2 / zero2 / shift2 (source-row order), or nullptr
   BhqLayout L;           // BHQ: L.k = 0 selects the general plan (slot, tau)
@@ -221,30 +226,33 @@ hipError_t launch_quant_nat_pair(const QuantParams& p0, const QuantParams& p1, h
 hipError_t launch_quant_fused(const QuantParams& pg, int mode, const QuantParams& px, const QuantParams& pw,
                               hipStream_t s);
 
-// Narrow transposing per-tensor quantizer (conv activations and Q_b1 of a
-// conv gradient): logical [rows, cols], row r of the output taken from source
-// row perm[r / blk] * blk + r % blk; codes [cols][ldt], rows >= rows get 0.
-struct NarrowQParams {
-  const float* x;
-  int64_t rows, cols;
-  const int32_t* perm;
-  int64_t blk;
+// Conv layer: X codes in pixel order, cp bytes per pixel (channels past c are
+// zero codes).  cp = 4: each image row has wp pixels, the image at pad, zero
+// codes around it.
+struct PixelQParams {
+  const float* x;  // [pixels][c]
+  int64_t words;   // output words (4 bytes)
+  int c, cp, w, wp, pad;
   int bits;
-  int stoch;
-  uint64_t seed;
-  uint32_t stream;
   const float* scale;
   const float* zero;
-  int8_t* q_t;
-  int64_t ldt;
-  int64_t vblk;  // rows of each block of blk that exist in x (the rest are zero codes); 0: blk
-  int rowscale;  // scale / zero per block (indexed by the block's source block), else per tensor
-  // 2-D blocks (gw > 0, replaces vblk): row br of a block is (y, x) = (br / gw,
-  // br % gw) of a grid with rows of gw; it exists iff y < gho and x < gwo and
-  // reads source row y gwo + x of its block
-  int64_t gw, gwo, gho;
+  int8_t* q;
 };
-hipError_t launch_quant_narrow_t(const NarrowQParams& p, hipStream_t s);
+constexpr int64_t PIXQ_WORDS = 1024;  // words per block
+// W [o][tap][c] -> codes [c][(tap, o)], sums over o [(tap, c)]
+struct ConvWQParams {
+  const float* w;  // nullptr: none
+  int o, taps, c;
+  int bits;
+  const float* scale;
+  const float* zero;
+  int8_t* q;
+  int32_t* sum;
+};
+// Q_b2(G) (pixel-major natural codes) with Q_b1(G) (pg.q2_n) from one read of
+// G, Q_f(X) and Q_theta(W); without pg.q_nat Q_b1 and Q_f only.
+hipError_t launch_quant_conv(const QuantParams& pg, int mode, const PixelQParams& px, const ConvWQParams& pw,
+                             hipStream_t s);
 
 // ---- int8 contractions ---------------------------------------------------
 
@@ -262,10 +270,6 @@ struct GemmParams {
   const int8_t* B;  // [N, K] row stride ldb
   int64_t M, N, K, lda, ldb;
   int64_t Kp;       // K with the zero codes that pad both operands' rows (0: K, no padding)
-  // conv B row map (bmap_c > 0, fast K loop only): row j = (tap, c) with
-  // tap = (r, s) of a bmap_kw-wide kernel starts at B + (s bmap_c + c) ldb +
-  // r bmap_wp (shifted activation-code grids, see ConvGeom)
-  int64_t bmap_c, bmap_kw, bmap_wp;
   int64_t kchunk;   // K per split (multiple of 128 when split, <= 65536)
   int splits;
   int32_t* part;    // EPI_RAW_I32 output [splits][M][N]
@@ -343,40 +347,48 @@ constexpr int NUM_XCD = 8;  // accelerator dies of the GPU, each with its own L2
 struct ConvGeom {
   int n, c, h, w, o, kh, kw, stride, pad, ho, wo;
   int64_t npad;  // slots per input pixel in the grad_X rows (multiple of 64)
-  int64_t psp;   // K pitch of a slot's output pixels in the grad_W operands (ho wo, or
-                 // ho wo rounded up to 128 with zero codes after them when Q_b1 is per sample;
-                 // the grid's ghp gwp rounded up to 128 for the implicit form)
-  // implicit grad_W (gwp > 0, stride 1): output pixel (y, x) of slot n is K
-  // index n psp + y gwp + x of Q_b1 (zero codes elsewhere); the activation
-  // codes sit on a zero-halo grid of ghp = h + 2 pad rows of gwp bytes (input
-  // pixel (iy, ix) at (iy + pad, ix + pad)), stored kw times [s][c][ldx], copy
-  // s shifted left by s bytes, so that tap (r, s) reads copy s at K offset
-  // r gwp: no im2col matrix
-  int64_t gwp, ghp, ldx;
+  // X codes in pixel order: cp bytes per pixel (4 for at most 4 channels, else
+  // the channels rounded up to 16); cp = 4: image rows of wp pixels with a
+  // horizontal halo of zero codes
+  int cp, wp;
 };
-hipError_t launch_conv_wq(const float* W, const ConvGeom& g, int bits, const float* scale, const float* zero,
-                          int8_t* wq_t, int32_t* swq, hipStream_t s);
-hipError_t launch_conv_im2col_w(const ConvGeom& g, const int8_t* xq_t, int8_t* bw, int64_t ldb, int32_t* xs,
-                                int32_t* sumB, hipStream_t s);
-hipError_t launch_conv_tapsums(const ConvGeom& g, const int8_t* q1_t, int64_t ldq, int32_t* qs, int32_t* sumA_tap,
-                               int32_t* count_tap, hipStream_t s);
-hipError_t launch_conv_gradw_reduce(const GemmParams& p, const ConvGeom& g, const int32_t* sumA_tap,
-                                    const int32_t* count_tap, hipStream_t s);
-// per-sample Q_b1 (K-blocked grad_W): slot weights dA = 1 / s, zA = z + half / s
-// and their sum; float64 weighted code sums over slots and their tap
-// rectangles; the weighted reduction of the per-slot int32 contractions
-struct ConvPsqSums {
-  double *dA, *zA, *zsum;  // [n], [n], [1]
-  double *qw, *xw;         // [o][ho wo], [c][h w]
-  double *WA, *WB;         // [o][taps], [(tap, c)]
+// grad_W (conv_gradw.hip): Q_b1 codes [pixel][o] and X codes in pixel order,
+// both in sample order; partial sums over splits of the output pixels, then the
+// reduction with the zero-point terms.
+struct ConvGradwParams {
+  const int8_t* q1;
+  const int8_t* xq;
+  int64_t Np;         // partial-sum columns (conv_gradw_cols)
+  int64_t per_split;  // pixels per split (per-sample Q_b1: samples)
+  int splits;
+  int32_t* part;      // [splits][o][Np]
+  int32_t* sumB;      // [Np] X code sums over each column's valid pixels (cleared before)
+  int32_t* qs;        // [ho wo][o] Q_b1 code sums over the samples
+  int32_t* sumA;      // [tap][o] ... over the tap's valid pixels
+  // per-sample Q_b1: the same in float64, weighted by 1 / s_n (sumB: by z_n + half / s_n)
+  double* partd;
+  double* sumBd;      // [splits][2][Np]
+  double* qsd;
+  double* sumAd;
+  double* zsum;       // [1] sum of z_n + half / s_n
+  const float* scaleA;  // [1], or [n] per sample
+  const float* zeroA;
+  int halfA;
+  const float* scaleB;
+  const float* zeroB;
+  int halfB;
+  float* out;         // [o][tap][c]
 };
-hipError_t launch_conv_psq_sums(const ConvGeom& g, const float* scale, const float* zero, const int32_t* perm,
-                                int half, const int8_t* q1_t, int64_t ldq, const int8_t* xq_t, const ConvPsqSums& ps,
-                                int32_t* count_tap, hipStream_t s);
-hipError_t launch_conv_gradw_psq_reduce(const GemmParams& p, const ConvGeom& g, const ConvPsqSums& ps,
-                                        const int32_t* count_tap, hipStream_t s);
-hipError_t launch_conv_gradx_prep(const ConvGeom& g, const int8_t* q2, const int32_t* swq, int32_t* sg, int32_t* rs,
-                                  int32_t* ct,
+int64_t conv_gradw_cols(const ConvGeom& g);
+void conv_gradw_splits(const ConvGeom& g, bool psq, int64_t& per_split, int& splits);
+hipError_t launch_conv_gradw(const ConvGradwParams& p, const ConvGeom& g, bool psq, hipStream_t s);
+// Zero-point sums of grad_W, and the row sums sg [pixel][slot] of Q_b2 (sg = nullptr: none).
+hipError_t launch_conv_sums(const ConvGradwParams& p, const ConvGeom& g, bool psq, const int8_t* q2, int32_t* sg,
+                            hipStream_t s);
+hipError_t launch_conv_gradw_reduce(const ConvGradwParams& p, const ConvGeom& g, bool psq, hipStream_t s);
+// Per (input pixel, slot) the sums of sg, and per (input pixel, channel) of
+// swq, over the taps that reach the pixel; their number in cnt.
+hipError_t launch_conv_gradx_prep(const ConvGeom& g, const int32_t* swq, const int32_t* sg, int32_t* rs, int32_t* ct,
                                   int32_t* cnt, hipStream_t s);
 hipError_t launch_conv_gradx(const GemmParams& p, int epi, const ConvGeom& g, const int8_t* q2, const int32_t* rs,
                              const int32_t* ct, const int32_t* cnt, hipStream_t s);

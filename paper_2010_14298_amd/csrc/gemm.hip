@@ -67,7 +67,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
   if (p.splits > 1 && p.splits % NUM_XCD == 0) {
     // split-K: blocks go to the XCDs round robin in launch order; give one
     // XCD every tile of its splits, so that the tiles sharing a split's A
-    // panel (and, for the conv taps, overlapping B rows) meet in its L2
+    // panel meet in its L2
     const int64_t T = tiles_m * tiles_n;
     const int64_t L = (int64_t)blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
     const int64_t j = L / NUM_XCD;
@@ -476,7 +476,6 @@ static hipError_t launch_gemm_t(GemmParams p, hipStream_t s) {
     }
   }
   if (p.packedA) return hipErrorInvalidValue;
-  if (p.bmap_c > 0 && (!fast || (p.bmap_wp & 15) != 0)) return hipErrorInvalidValue;  // mapped rows: fast loop only
   if (fast)
     hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, true>), grid, dim3(C::THREADS), 0, s, p);
   else

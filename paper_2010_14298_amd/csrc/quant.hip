@@ -97,6 +97,12 @@ __device__ __forceinline__ MinMax block_minmax(float mn, float mx, int bad) {
 // atomics: the finalize block combines the partials.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void stats_kernel(StatsPlan sp) {
+  if ((int64_t)blockIdx.x >= sp.block_start[sp.nseg]) {
+    // the blocks after the statistics clear an array of counters
+    const int64_t z0 = ((int64_t)blockIdx.x - sp.block_start[sp.nseg]) * STATS_ZERO;
+    for (int64_t i = z0 + threadIdx.x; i < z0 + STATS_ZERO && i < sp.zero_n; i += blockDim.x) sp.zero[i] = 0;
+    return;
+  }
   int si = 0;
   while (si + 1 < sp.nseg && (int64_t)blockIdx.x >= sp.block_start[si + 1]) ++si;
   const StatsSeg g = sp.seg[si];
@@ -163,6 +169,7 @@ hipError_t launch_stats(StatsPlan sp, hipStream_t s) {
     total += stats_partials(sp.seg[i]);
   }
   sp.block_start[sp.nseg] = total;
+  total += (sp.zero_n + STATS_ZERO - 1) / STATS_ZERO;
   if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
   hipLaunchKernelGGL(stats_kernel, dim3((unsigned)total), dim3(256), 0, s, sp);
   return hipGetLastError();
@@ -717,7 +724,9 @@ __device__ __forceinline__ void rne4(const float (&y)[4], float Bf, uint32_t hof
 // instead of in natural order ([rows, cols], row sums).
 // One 64 x 256 tile: column tile bx, slot tile by.
 // H2: the second (transposed, stochastic) quantizer of the same rows, Q_b1:
-// 0 none, 1 per tensor, 2 per row with power-of-two shifted codes.
+// 0 none, 1 per tensor, 2 per row with power-of-two shifted codes; 3: natural
+// instead, codes [row][cols] in source-row order (per tensor, or per row with
+// p.row2) and column sums; 4: as 3, without the primary quantizer.
 template <int MODE, int K, int H2, bool VEC, bool TRANS, bool SD = false>
 __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int64_t by) {
   const int lane = threadIdx.x & 63;
@@ -726,6 +735,7 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
   const int64_t slot0 = tile0 + wave * QT_ROWS_PER_WAVE;
   const int64_t c0 = bx * QT_COLS + lane * 4;
   const int64_t rows = p.rows, cols = p.cols;
+  constexpr bool PRIM = H2 != 4, SECT = H2 == 1 || H2 == 2, SECN = H2 >= 3;
   const int B = (1 << p.bits) - 1;
   const int half = 1 << (p.bits - 1);
   const bool lane_ok = c0 < cols;
@@ -811,6 +821,11 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
       lshift2 = p.shift2[lrow];
     }
   }
+  if constexpr (SECN) {
+    const int32_t at = p.row2 ? lrow : 0;
+    lscale2 = p.scale2[at];
+    lzero2 = p.zero2[at];
+  }
   auto row_scale = [&](int r) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lscale), r)); };
   auto row_zero = [&](int r) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lzero), r)); };
   // ---- block Householder (K >= 16): a group spans K / 16 waves.  Its column
@@ -889,8 +904,9 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
       tq[j][w] = 0u;
       tq2[j][w] = 0u;
     }
-  const float s_t = (MODE == QM_TENSOR) ? p.scale[0] : 0.0f;
-  const float z_t = (MODE == QM_TENSOR) ? p.zero[0] : 0.0f;
+  const float s_t = (MODE == QM_TENSOR && PRIM) ? p.scale[0] : 0.0f;
+  const float z_t = (MODE == QM_TENSOR && PRIM) ? p.zero[0] : 0.0f;
+  int32_t csn[4] = {0, 0, 0, 0};  // column sums of natural second codes
   float Bf2 = 0.0f, s2 = 0.0f, z2 = 0.0f;
   uint32_t hoff2 = 0u;
   if constexpr (H2 != 0) {
@@ -1030,11 +1046,13 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
       continue;
     }
     int32_t t[4];
-    // with a second quantizer the first is stochastic too (launch_quant checks)
-    if (H2 != 0 || p.stoch)
-      sr4<VEC>(y, e0, p.seed, p.stream, Bf, hoff, t);
-    else
-      rne4(y, Bf, hoff, t);
+    // with a second quantizer the first is stochastic too (the launches check)
+    if constexpr (PRIM) {
+      if (H2 != 0 || p.stoch)
+        sr4<VEC>(y, e0, p.seed, p.stream, Bf, hoff, t);
+      else
+        rne4(y, Bf, hoff, t);
+    }
     if constexpr (MODE == QM_ROW) {
       if (p.shift && ok) {
         const int sh = p.shift[slot];
@@ -1048,10 +1066,10 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
       // rounds' products with the call above)
       float s2r = s2, z2r = z2;
       int sh2 = 0;
-      if constexpr (H2 == 2) {
+      if constexpr (H2 != 1) {
         s2r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lscale2), r));
         z2r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lzero2), r));
-        sh2 = __builtin_amdgcn_readlane(lshift2, r);
+        if constexpr (H2 == 2) sh2 = __builtin_amdgcn_readlane(lshift2, r);
       }
       float y2[4];
 #pragma unroll
@@ -1062,12 +1080,20 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
 #pragma unroll
         for (int j = 0; j < 4; ++j) t2[j] = shift_top(t2[j], sh2);
       }
-      if (ok) {
+      if constexpr (SECN) {
+        if (ok && lane_ok) {
+          // cols % 16 == 0 (checked at launch): whole words
+          *reinterpret_cast<uint32_t*>(p.q2_n + (int64_t)src_row(r) * cols + c0) = pack_top4(t2[0], t2[1], t2[2], t2[3]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) csn[j] = __builtin_amdgcn_sdot4(t2[j], 0x01000000, csn[j], false);
+        }
+      } else if (ok) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) tq2[j][r >> 2] = insert_top(tq2[j][r >> 2], t2[j], r & 3);
       }
     }
-    if constexpr (!TRANS) {
+    if constexpr (!PRIM) {
+    } else if constexpr (!TRANS) {
       const uint32_t w = pack_top4(t[0], t[1], t[2], t[3]);
       if (p.q_nat && ok && nat_ok) {
         int8_t* dst = p.q_nat + nat0 + r * nat_step;
@@ -1117,7 +1143,7 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
           if (p.ldt == 0 && r < nok) dst[r] = (int8_t)((tq[j][r >> 2] >> (8 * (r & 3))) & 255);
       }
     }
-    if constexpr (H2 != 0) {
+    if constexpr (SECT) {
       int8_t* dst = p.q2_t + col * ldt + slot0;
       if (tvec) {
         *reinterpret_cast<uint4*>(dst) = make_uint4(tq2[j][0], tq2[j][1], tq2[j][2], tq2[j][3]);
@@ -1137,8 +1163,9 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         if constexpr (TRANS) cs = sum4_i8(tq[j][w], cs);
-        if constexpr (H2 != 0) cs2 = sum4_i8(tq2[j][w], cs2);
+        if constexpr (SECT) cs2 = sum4_i8(tq2[j][w], cs2);
       }
+      if constexpr (SECN) cs2 = csn[j];
       s_csum[0][wave][lane * 4 + j] = cs;
       s_csum[1][wave][lane * 4 + j] = cs2;
     }
@@ -1310,6 +1337,181 @@ hipError_t launch_quant_fused(const QuantParams& pg, int mode, const QuantParams
     case 16: return launch_quant_fused_k<QM_BHQ, 16>(pg, px, pw, s);
     case 32: return launch_quant_fused_k<QM_BHQ, 32>(pg, px, pw, s);
     case 64: return launch_quant_fused_k<QM_BHQ, 64>(pg, px, pw, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// conv layer: Q_b2(G) (pixel-major) and Q_b1(G) (natural) from one read of G,
+// Q_f(X) in pixel order and Q_theta(W), one launch
+// ---------------------------------------------------------------------------
+// Q_f(X): one word of four channels per thread and step; channels past c and
+// halo pixels get zero codes.  c == cp without a halo (and an aligned X): the
+// words follow each other in memory on both sides.
+__device__ __forceinline__ void quant_pixels(const PixelQParams& p, int64_t block) {
+  const int t = threadIdx.x;
+  const int64_t base = block * PIXQ_WORDS;
+  const float s = p.scale[0], z = p.zero[0];
+  const float Bf = (float)((1 << p.bits) - 1);
+  const uint32_t hoff = (uint32_t)(1 << (p.bits - 1)) << 24;
+  constexpr int U = PIXQ_WORDS / 256;
+  float v[U][4];
+  int nch[U];
+  if (p.c == p.cp && p.cp != 4 && ((uintptr_t)p.x & 15) == 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t w = base + t + 256 * u;
+      const float4 f = *reinterpret_cast<const float4*>(p.x + 4 * (w < p.words ? w : 0));
+      v[u][0] = f.x;
+      v[u][1] = f.y;
+      v[u][2] = f.z;
+      v[u][3] = f.w;
+      nch[u] = 4;
+    }
+  } else {
+    // (row of wpr words, word in it): pixels of cp / 4 words, or image rows of
+    // wp one-word pixels with a halo
+    const bool halo = p.cp == 4;
+    const uint32_t wpr = halo ? (uint32_t)p.wp : (uint32_t)p.cp / 4;
+    const int64_t row0 = base / wpr;
+    const uint32_t rem0 = (uint32_t)(base - row0 * wpr);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t l = rem0 + t + 256 * u, dr = l / wpr, k = l - dr * wpr;
+      const int64_t row = row0 + dr;
+      int64_t src;
+      if (halo) {
+        const int ix = (int)k - p.pad;
+        nch[u] = ix >= 0 && ix < p.w ? p.c : 0;
+        src = (row * p.w + ix) * p.c;
+      } else {
+        nch[u] = p.c - 4 * (int)k;
+        src = row * p.c + 4 * (int64_t)k;
+      }
+      if (base + t + 256 * u >= p.words) nch[u] = 0;
+      if (nch[u] >= 4) {
+        const Float4U f = *reinterpret_cast<const Float4U*>(p.x + src);
+        v[u][0] = f.x;
+        v[u][1] = f.y;
+        v[u][2] = f.z;
+        v[u][3] = f.w;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] = p.x[j < nch[u] ? src + j : 0];
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t w = base + t + 256 * u;
+    if (w >= p.words) continue;
+    float y[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = s * (v[u][j] - z);
+    int32_t q[4];
+    rne4(y, Bf, hoff, q);
+    uint32_t m = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j < nch[u]) m |= 0xFFu << (8 * j);
+    *reinterpret_cast<uint32_t*>(p.q + 4 * w) = pack_top4(q[0], q[1], q[2], q[3]) & m;
+  }
+}
+
+// Q_theta(W): codes [c][(tap, o)] and their sums over o per (tap, c).  A block
+// takes one tap and 16 channels: 64-byte runs of W rows in, 16-byte runs of
+// codes out, transposed through LDS 256 output channels at a time.
+__device__ __forceinline__ void quant_conv_w(const ConvWQParams& p, int64_t block) {
+  __shared__ __attribute__((aligned(16))) int8_t sq[16][256 + 16];
+  const int t = threadIdx.x;
+  const int cb = (p.c + 15) / 16;
+  const int tap = (int)(block / cb), ch0 = 16 * (int)(block % cb);
+  const int B = (1 << p.bits) - 1, half = 1 << (p.bits - 1);
+  const float s = p.scale[0], z = p.zero[0];
+  const int64_t K = (int64_t)p.taps * p.o;
+  const int cl = t & 15, ol = t >> 4;
+  const int ch = min(ch0 + cl, p.c - 1);
+  int sum = 0;  // of channel ch0 + ol (the store's assignment), this thread's runs
+  for (int o0 = 0; o0 < p.o; o0 += 256) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int o = min(o0 + ol + 16 * u, p.o - 1);
+      v[u] = p.w[((int64_t)o * p.taps + tap) * p.c + ch];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 16; ++u) sq[cl][ol + 16 * u] = (int8_t)(rne_code(s * (v[u] - z), B) - half);
+    __syncthreads();
+    // o is a multiple of 16: thread (ol, cl) stores run cl of channel ch0 + ol
+    if (o0 + 16 * cl < p.o && ch0 + ol < p.c) {
+      const uint4 q = *reinterpret_cast<const uint4*>(&sq[ol][16 * cl]);
+      *reinterpret_cast<uint4*>(p.q + (int64_t)(ch0 + ol) * K + (int64_t)tap * p.o + o0 + 16 * cl) = q;
+      sum = sum4_i8(q.x, sum4_i8(q.y, sum4_i8(q.z, sum4_i8(q.w, sum))));
+    }
+  }
+#pragma unroll
+  for (int h = 8; h > 0; h >>= 1) sum += __shfl_xor(sum, h);
+  if (cl == 0 && ch0 + ol < p.c) p.sum[(int64_t)tap * p.c + ch0 + ol] = sum;
+}
+
+// Blocks [0, nbw) the weights; of the rest every period-th (while they last) a
+// run of X words, the others the gradient tiles in order.
+template <int MODE, int K, int H2, bool VEC>
+__global__ __launch_bounds__(256) void quant_conv_kernel(QuantParams pg, PixelQParams px, ConvWQParams pw, int64_t nbw,
+                                                         int64_t nbx, int64_t period, int64_t ctg) {
+  int64_t b = blockIdx.x;
+  if (b < nbw) {
+    quant_conv_w(pw, b);
+    return;
+  }
+  b -= nbw;
+  if (b % period == period - 1 && b / period < nbx) {
+    quant_pixels(px, b / period);
+  } else {
+    const int64_t before = (b + 1) / period < nbx ? (b + 1) / period : nbx;
+    const int64_t t = b - before;
+    quant_tile<MODE, K, H2, VEC, false>(pg, t % ctg, t / ctg);
+  }
+}
+
+template <int MODE, int K, int H2>
+static hipError_t launch_quant_conv_k(const QuantParams& pg, const PixelQParams& px, const ConvWQParams& pw,
+                                      hipStream_t s) {
+  const int64_t ctg = col_tiles(pg), nbg = ctg * slot_tiles(pg);
+  const int64_t nbx = (px.words + PIXQ_WORDS - 1) / PIXQ_WORDS;
+  const int64_t nbw = pw.w ? (int64_t)pw.taps * ((pw.c + 15) / 16) : 0;
+  if (nbg + nbx + nbw > 0x7FFFFFFF || nbx < 1) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(nbg + nbx + nbw));
+  const int64_t period = (nbg + nbx) / nbx;
+  if (quant_vec(pg))
+    hipLaunchKernelGGL((quant_conv_kernel<MODE, K, H2, true>), grid, dim3(256), 0, s, pg, px, pw, nbw, nbx, period, ctg);
+  else
+    hipLaunchKernelGGL((quant_conv_kernel<MODE, K, H2, false>), grid, dim3(256), 0, s, pg, px, pw, nbw, nbx, period,
+                       ctg);
+  return hipGetLastError();
+}
+
+hipError_t launch_quant_conv(const QuantParams& pg, int mode, const PixelQParams& px, const ConvWQParams& pw,
+                             hipStream_t s) {
+  if (!pg.q2_n || pg.q2_t || pg.q_t || pg.sum_t || pg.shift2 || pg.packed || pg.ldn || pg.ldt || (pg.cols & 15) != 0 ||
+      pg.stoch != 1 || px.c < 1 || px.c > px.cp || (px.cp != 4 && (px.cp & 15) != 0) || (px.cp == 4 && px.wp < px.w) ||
+      (((uintptr_t)pg.q2_n | (uintptr_t)px.q) & 3) != 0)
+    return hipErrorInvalidValue;
+  if (!pg.q_nat) return launch_quant_conv_k<QM_TENSOR, 0, 4>(pg, px, pw, s);
+  if (pg.pm_o < 4 || (pg.pm_o & 3) != 0 || pg.cols % pg.pm_o != 0 || !pw.w || ((uintptr_t)pw.q & 15) != 0)
+    return hipErrorInvalidValue;
+  if (mode == QM_TENSOR) return launch_quant_conv_k<QM_TENSOR, 0, 3>(pg, px, pw, s);
+  if (mode == QM_ROW) return launch_quant_conv_k<QM_ROW, 0, 3>(pg, px, pw, s);
+  switch (pg.L.k) {
+    case 0: return pg.slot && pg.tau ? launch_quant_conv_k<QM_BHQ, 0, 3>(pg, px, pw, s) : hipErrorInvalidValue;
+    case 1: return launch_quant_conv_k<QM_BHQ, 1, 3>(pg, px, pw, s);
+    case 2: return launch_quant_conv_k<QM_BHQ, 2, 3>(pg, px, pw, s);
+    case 4: return launch_quant_conv_k<QM_BHQ, 4, 3>(pg, px, pw, s);
+    case 8: return launch_quant_conv_k<QM_BHQ, 8, 3>(pg, px, pw, s);
+    case 16: return launch_quant_conv_k<QM_BHQ, 16, 3>(pg, px, pw, s);
+    case 32: return launch_quant_conv_k<QM_BHQ, 32, 3>(pg, px, pw, s);
+    case 64: return launch_quant_conv_k<QM_BHQ, 64, 3>(pg, px, pw, s);
     default: return hipErrorInvalidValue;
   }
 }
