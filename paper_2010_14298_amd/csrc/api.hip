@@ -421,7 +421,8 @@ fqt_status check_conv_shape(const fqt_conv_shape& sh) {
 // wide enough for the last chunk.
 ConvGeom conv_geom(const fqt_conv_shape& sh) {
   ConvGeom g{sh.n, sh.c, sh.h, sh.w, sh.o, sh.kh, sh.kw, sh.stride, sh.pad, sh.ho, sh.wo, 0, 0, 0};
-  g.npad = ((int64_t)sh.n + 63) / 64 * 64;
+  // at most 32 samples: several pixels share a 64-row unit of the grad_X contraction
+  g.npad = sh.n <= 16 ? 16 : (sh.n <= 32 ? 32 : ((int64_t)sh.n + 63) / 64 * 64);
   g.cp = (sh.c + 15) / 16 * 16;
   if (sh.c <= 4) {
     const int64_t full = (int64_t)sh.w + 2 * (int64_t)sh.pad;
@@ -440,8 +441,8 @@ struct ConvWs {
   StatsSeg sx_seg, sw_seg, sg_seg;
   float *rmin, *rmax;
   int8_t *xq, *wq_t, *q2, *q1;
-  int32_t *swq, *sg, *rs, *ct, *cnt;
-  int32_t* counters;  // cleared before the quantizers: gw.sumB, gw.qs
+  int32_t *swq, *sg;
+  int32_t* counters;  // cleared before the quantizers: 16 zero bytes, gw.sumB, gw.qs
   int64_t ncounters;
   int64_t xbytes;
   float *sx, *zx, *sw, *zw, *sg1, *zg1, *sg2, *zg2;
@@ -474,9 +475,6 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   w.q1 = c.take<int8_t>(N * howo * g.o);
   w.swq = c.take<int32_t>(taps * g.c);
   w.sg = c.take<int32_t>(N * howo);
-  w.rs = c.take<int32_t>(N * hw);
-  w.ct = c.take<int32_t>(hw * g.c);
-  w.cnt = c.take<int32_t>(hw);
   w.sx = c.take<float>(1);
   w.zx = c.take<float>(1);
   w.sw = c.take<float>(1);
@@ -503,12 +501,14 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
     p.qsd = c.take<double>(howo * g.o);
     p.sumAd = c.take<double>(taps * g.o);
     p.zsum = c.take<double>(1);
+    w.ncounters = 4;
+    w.counters = c.take<int32_t>(w.ncounters);
   } else {
     p.part = c.take<int32_t>(parts);
-    w.ncounters = p.Np + howo * g.o;
+    w.ncounters = 4 + p.Np + howo * g.o;
     w.counters = c.take<int32_t>(w.ncounters);
-    p.sumB = w.counters;
-    p.qs = w.counters ? w.counters + p.Np : nullptr;
+    p.sumB = w.counters ? w.counters + 4 : nullptr;
+    p.qs = w.counters ? w.counters + 4 + p.Np : nullptr;
     p.sumA = c.take<int32_t>(taps * g.o);
   }
   return w;
@@ -1226,7 +1226,6 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
     return FQT_OK;
   }
   tr.begin(7);
-  FQT_TRY(launch_conv_gradx_prep(g, w.swq, w.sg, w.rs, w.ct, w.cnt, s));
   GemmParams gx{};
   gx.B = w.wq_t;
   gx.M = hw * g.npad;
@@ -1250,7 +1249,8 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
     gx.slot = w.bhq.slot;
     gx.tbuf = w.tbuf;
     gx.ldt = g.c;
-    FQT_TRY(launch_conv_gradx(gx, EPI_BHQT, g, w.q2, w.rs, w.ct, w.cnt, s));
+    FQT_TRY(launch_conv_gradx(gx, EPI_BHQT, g, w.q2, reinterpret_cast<const int8_t*>(w.counters),
+                              w.sg, w.swq, s));
     InverseParams ip{};
     ip.T = w.tbuf;
     ip.ldt = g.c;
@@ -1267,7 +1267,8 @@ fqt_status fqt_conv_backward_im2col(const float* X, const float* W, const float*
     ip.obstride = 1;
     FQT_TRY(launch_bhq_inverse(ip, s));
   } else {
-    FQT_TRY(launch_conv_gradx(gx, bhq ? EPI_BHQ : EPI_ROW, g, w.q2, w.rs, w.ct, w.cnt, s));
+    FQT_TRY(launch_conv_gradx(gx, bhq ? EPI_BHQ : EPI_ROW, g, w.q2, reinterpret_cast<const int8_t*>(w.counters),
+                              w.sg, w.swq, s));
   }
   tr.end(7);
   return FQT_OK;

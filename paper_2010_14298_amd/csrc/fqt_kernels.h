@@ -346,7 +346,7 @@ constexpr int NUM_XCD = 8;  // accelerator dies of the GPU, each with its own L2
 // ---- conv ----------------------------------------------------------------
 struct ConvGeom {
   int n, c, h, w, o, kh, kw, stride, pad, ho, wo;
-  int64_t npad;  // slots per input pixel in the grad_X rows (multiple of 64)
+  int64_t npad;  // slots per input pixel in the grad_X rows (16, 32 or a multiple of 64)
   // X codes in pixel order: cp bytes per pixel (4 for at most 4 channels, else
   // the channels rounded up to 16); cp = 4: image rows of wp pixels with a
   // horizontal halo of zero codes
@@ -386,11 +386,9 @@ hipError_t launch_conv_gradw(const ConvGradwParams& p, const ConvGeom& g, bool p
 hipError_t launch_conv_sums(const ConvGradwParams& p, const ConvGeom& g, bool psq, const int8_t* q2, int32_t* sg,
                             hipStream_t s);
 hipError_t launch_conv_gradw_reduce(const ConvGradwParams& p, const ConvGeom& g, bool psq, hipStream_t s);
-// Per (input pixel, slot) the sums of sg, and per (input pixel, channel) of
-// swq, over the taps that reach the pixel; their number in cnt.
-hipError_t launch_conv_gradx_prep(const ConvGeom& g, const int32_t* swq, const int32_t* sg, int32_t* rs, int32_t* ct,
-                                  int32_t* cnt, hipStream_t s);
-hipError_t launch_conv_gradx(const GemmParams& p, int epi, const ConvGeom& g, const int8_t* q2, const int32_t* rs,
-                             const int32_t* ct, const int32_t* cnt, hipStream_t s);
+// sg: row sums [output pixel][slot] of the Q_b2 codes; swq: W code sums over o
+// [(tap, c)]; zero16: 16 zero bytes after q2 in the same workspace.
+hipError_t launch_conv_gradx(const GemmParams& p, int epi, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,
+                             const int32_t* sg, const int32_t* swq, hipStream_t s);
 
 }  // namespace fqt
