@@ -545,11 +545,11 @@ __global__ __launch_bounds__(512, 2) void conv_gradx_kernel(GemmParams p, ConvGe
           o[j] = (float)v;
         }
         if (vec) {
-          *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
+          stream_store4(dst, make_float4(o[0], o[1], o[2], o[3]));
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            if (col + j < g.c) dst[j] = o[j];
+            if (col + j < g.c) stream_store(dst + j, o[j]);
         }
       }
     }

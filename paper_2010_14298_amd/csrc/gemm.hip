@@ -43,7 +43,7 @@ struct GroupStage {
 // it) entries where the mask is not positive are zero.
 __device__ __forceinline__ void store_masked(const GemmParams& p, int64_t idx, double v) {
   const float f = (float)v;
-  p.out[idx] = (p.mask && !(p.mask[idx] > 0.0f)) ? 0.0f : f;
+  stream_store(p.out + idx, (p.mask && !(p.mask[idx] > 0.0f)) ? 0.0f : f);
 }
 
 template <class C, int EPI>
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
           const int64_t col = n0 + wn * C::WN + j * 32 + lrow;
           if (col < p.N) {
             const float v = (float)(dAB * (double)acc[i][j][r] + rterm + cterm[j]);
-            p.out[row * p.ldo + col] = (p.relu && !(v > 0.0f)) ? 0.0f : v;
+            stream_store(p.out + row * p.ldo + col, (p.relu && !(v > 0.0f)) ? 0.0f : v);
           }
         }
       }
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
             f.z = m.z > 0.0f ? f.z : 0.0f;
             f.w = m.w > 0.0f ? f.w : 0.0f;
           }
-          *reinterpret_cast<float4*>(p.out + idx) = f;
+          stream_store4(p.out + idx, f);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
