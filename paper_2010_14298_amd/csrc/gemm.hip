@@ -77,8 +77,10 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
     tile = xcd_tile(blockIdx.x, tiles_m * tiles_n);
     split = blockIdx.y;
   }
-  const int64_t m0 = (tile / tiles_n) * C::BM;
-  const int64_t n0 = (tile % tiles_n) * C::BN;
+  int64_t tm, tn;
+  tile_mn(tile, tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = tm * C::BM;
+  const int64_t n0 = tn * C::BN;
   const int64_t kbeg = (int64_t)split * p.kchunk;
   const int64_t Kp = p.Kp > 0 ? p.Kp : p.K;
   const int64_t kend = (kbeg + p.kchunk < Kp) ? kbeg + p.kchunk : Kp;
