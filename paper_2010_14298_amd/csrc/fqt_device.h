@@ -242,15 +242,19 @@ __device__ __forceinline__ double group_term(float s1, float s2, int64_t k) {
 // launch reads again: nontemporal, so that they neither push the operand codes
 // out of L2 nor leave the caches full of dirty lines for the next launch to
 // write back.  Against plain stores: forward 8192 x 1024 -> 4096 119.3 -> 99.7
-// us, FFN layer 212.7 -> 209 (grad_W alone) and 202.5 (both), 3x3 s2 128ch
-// 56x56 b256 528 -> 478, 3x3 64ch 56x56 b128 262 -> 247, 3001 tokens 123.6 ->
-// 117; a following layer that reads the outputs gains too (3-layer MLP 1.530
-// -> 1.488 ms a step).
+// us, FFN layer 213.4 -> 202.5, 3x3 s2 128ch 56x56 b256 528 -> 478, 3x3 64ch
+// 56x56 b128 262 -> 247, 3001 x 1024 -> 4096 123.6 -> 117.0; a following layer
+// that reads the outputs gains too (3-layer MLP 1.530 -> 1.488 ms a step).  A
+// choice between both kinds by the output's size doubles the epilogues' code
+// and slows the smallest layers (128 x 256 -> 256 37.1 -> 39.6 us).
 typedef float v4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void stream_store(float* p, float v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void stream_store4(float* p, const float4& v) {
-  __builtin_nontemporal_store(v4f{v.x, v.y, v.z, v.w}, reinterpret_cast<v4f*>(p));
+__device__ __forceinline__ void stream_store4(float* p, const float4& f) {
+  __builtin_nontemporal_store(v4f{f.x, f.y, f.z, f.w}, reinterpret_cast<v4f*>(p));
 }
+// Keeps the two sides of a branch apart: the compiler merges an ordinary and a
+// nontemporal access to one ordinary access.
+__device__ __forceinline__ void nt_fence() { asm volatile(""); }
 
 // Status word bits (first word of every workspace).
 constexpr uint32_t STATUS_NONFINITE = 1u;

@@ -179,6 +179,7 @@ hipError_t launch_bhq_inverse(const InverseParams& p, hipStream_t s);
 struct QuantParams {
   const float* x;
   int64_t rows, cols;
+  int nt;               // the launch's inputs are read nontemporally (set at launch)
   const int32_t* perm;  // slot -> source row; nullptr = identity
   int bits;
   int stoch;
@@ -220,7 +221,7 @@ hipError_t launch_quant(const QuantParams& p, int mode, hipStream_t s);
 // The seed batch of one quantizer (natural layout, cols % 4 == 0).
 hipError_t launch_quant_seeds(const QuantParams& p, int mode, hipStream_t s);
 // Two per-tensor quantizations with natural outputs only, one launch.
-hipError_t launch_quant_nat_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s);
+hipError_t launch_quant_nat_pair(QuantParams p0, QuantParams p1, hipStream_t s);
 // The gradient quantizer pg (with its transposed second quantizer) and the
 // per-tensor transposed quantizers px, pw in one launch.
 hipError_t launch_quant_fused(const QuantParams& pg, int mode, const QuantParams& px, const QuantParams& pw,
@@ -233,6 +234,7 @@ struct PixelQParams {
   const float* x;  // [pixels][c]
   int64_t words;   // output words (4 bytes)
   int c, cp, w, wp, pad;
+  int nt;          // as QuantParams
   int bits;
   const float* scale;
   const float* zero;

@@ -15,6 +15,8 @@
 //              bifurcated Q_b1 of App. E) from the same read.
 #include <math.h>
 
+#include <type_traits>
+
 #include "fqt_device.h"
 #include "fqt_kernels.h"
 
@@ -770,34 +772,46 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
 
   // ---- load 16 rows x 4 columns
   float g[QT_ROWS_PER_WAVE][4];
+  auto load_rows = [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < QT_ROWS_PER_WAVE; ++r) {
-    const bool ok = r < nok;
-    const int32_t row = src_row(r);
-    const float* xr = p.x + (int64_t)row * cols;
-    if constexpr (VEC) {
-      if (ok && lane_ok) {
-        const float4 v = *reinterpret_cast<const float4*>(xr + c0);
-        g[r][0] = v.x;
-        g[r][1] = v.y;
-        g[r][2] = v.z;
-        g[r][3] = v.w;
+    for (int r = 0; r < QT_ROWS_PER_WAVE; ++r) {
+      const bool ok = r < nok;
+      const int32_t row = src_row(r);
+      const float* xr = p.x + (int64_t)row * cols;
+      if constexpr (VEC) {
+        if (ok && lane_ok) {
+          const v4f* at = reinterpret_cast<const v4f*>(xr + c0);
+          v4f v;
+          if constexpr (decltype(nt)::value)
+            v = __builtin_nontemporal_load(at);
+          else
+            v = *at;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) g[r][j] = v[j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) g[r][j] = 0.0f;
+        }
       } else {
+        if (ok && c0 + 3 < cols) {
+          const Float4U v = *reinterpret_cast<const Float4U*>(xr + c0);
+          g[r][0] = v.x;
+          g[r][1] = v.y;
+          g[r][2] = v.z;
+          g[r][3] = v.w;
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) g[r][j] = 0.0f;
-      }
-    } else {
-      if (ok && c0 + 3 < cols) {
-        const Float4U v = *reinterpret_cast<const Float4U*>(xr + c0);
-        g[r][0] = v.x;
-        g[r][1] = v.y;
-        g[r][2] = v.z;
-        g[r][3] = v.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) g[r][j] = (ok && c0 + j < cols) ? xr[c0 + j] : 0.0f;
+          for (int j = 0; j < 4; ++j) g[r][j] = (ok && c0 + j < cols) ? xr[c0 + j] : 0.0f;
+        }
       }
     }
+  };
+  if (VEC && p.nt) {
+    nt_fence();
+    load_rows(std::true_type{});
+    nt_fence();
+  } else {
+    load_rows(std::false_type{});
   }
 
   // per-slot scale and zero of the wave's 16 rows, lane l holding row l:
@@ -1235,9 +1249,19 @@ static bool pitch_ok(const QuantParams& p) {
   return true;
 }
 
+// The quantizer is the last reader of its float32 inputs in a step (the
+// statistics read them before).  Inputs that leave no room for themselves and
+// the codes in the 256 MB last-level cache are read nontemporally, so that the
+// codes stay in it for the contractions; smaller ones stay cached for whoever
+// reads them next.  With / without: FFN layer (184 MB of inputs) 200.3 / 208.3
+// us, 8192 x 4096 block Householder quantizer (134 MB) 75.0 / 79.2, 3x3 64ch
+// 56x56 b128 (206 MB) 240.6 / 246.9; 3x3 s2 128ch 56x56 b256 (514 MB) 475 / 478,
+// with the conv launch's order from the end 462 (the order alone: 475); 3001 x 1024 -> 4096 (78 MB) 121.0 / 117.7.
+static int quant_nt(int64_t floats) { return floats * 4 >= (int64_t)100 << 20; }
+
 template <int MODE, int K, bool VEC>
-static hipError_t launch_quant_fused_v(const QuantParams& pg, const QuantParams& px, const QuantParams& pw,
-                                       hipStream_t s) {
+static hipError_t launch_quant_fused_v(QuantParams pg, QuantParams px, QuantParams pw, hipStream_t s) {
+  pg.nt = px.nt = pw.nt = quant_nt(pg.rows * pg.cols + px.rows * px.cols + pw.rows * pw.cols);
   if (!pitch_ok(pg) || !pitch_ok(px) || !pitch_ok(pw)) return hipErrorInvalidValue;
   const int64_t ctg = col_tiles(pg), rtg = slot_tiles(pg);
   const int64_t ctx = col_tiles(px), rtx = slot_tiles(px);
@@ -1266,7 +1290,8 @@ static hipError_t launch_quant_fused_k(const QuantParams& pg, const QuantParams&
 }
 
 template <int MODE, int K>
-static hipError_t launch_quant_k(const QuantParams& p, hipStream_t s) {
+static hipError_t launch_quant_k(QuantParams p, hipStream_t s) {
+  p.nt = quant_nt(p.rows * p.cols);
   const int64_t ct = col_tiles(p), rt = slot_tiles(p);
   if (ct > 0x7FFFFFFF || rt > 65535 || !pitch_ok(p)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)ct, (unsigned)rt);
@@ -1306,7 +1331,8 @@ __global__ __launch_bounds__(256) void quant_nat2_kernel(QuantParams p0, QuantPa
     quant_tile<QM_TENSOR, 0, 0, VEC, false>(p1, (b - nb0) % ct1, (b - nb0) / ct1);
 }
 
-hipError_t launch_quant_nat_pair(const QuantParams& p0, const QuantParams& p1, hipStream_t s) {
+hipError_t launch_quant_nat_pair(QuantParams p0, QuantParams p1, hipStream_t s) {
+  p0.nt = p1.nt = quant_nt(p0.rows * p0.cols + p1.rows * p1.cols);
   for (const QuantParams* p : {&p0, &p1})
     if (!p->q_nat || p->q_t || p->sum_t || p->q2_t || p->packed || p->pm_o || !pitch_ok(*p)) return hipErrorInvalidValue;
   const int64_t ct0 = col_tiles(p0), ct1 = col_tiles(p1);
@@ -1358,15 +1384,27 @@ __device__ __forceinline__ void quant_pixels(const PixelQParams& p, int64_t bloc
   float v[U][4];
   int nch[U];
   if (p.c == p.cp && p.cp != 4 && ((uintptr_t)p.x & 15) == 0) {
+    auto load_words = [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t w = base + t + 256 * u;
-      const float4 f = *reinterpret_cast<const float4*>(p.x + 4 * (w < p.words ? w : 0));
-      v[u][0] = f.x;
-      v[u][1] = f.y;
-      v[u][2] = f.z;
-      v[u][3] = f.w;
-      nch[u] = 4;
+      for (int u = 0; u < U; ++u) {
+        const int64_t w = base + t + 256 * u;
+        const v4f* at = reinterpret_cast<const v4f*>(p.x + 4 * (w < p.words ? w : 0));
+        v4f f;
+        if constexpr (decltype(nt)::value)
+          f = __builtin_nontemporal_load(at);
+        else
+          f = *at;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] = f[j];
+        nch[u] = 4;
+      }
+    };
+    if (p.nt) {
+      nt_fence();
+      load_words(std::true_type{});
+      nt_fence();
+    } else {
+      load_words(std::false_type{});
     }
   } else {
     // (row of wpr words, word in it): pixels of cp / 4 words, or image rows of
@@ -1456,7 +1494,9 @@ __device__ __forceinline__ void quant_conv_w(const ConvWQParams& p, int64_t bloc
 }
 
 // Blocks [0, nbw) the weights; of the rest every period-th (while they last) a
-// run of X words, the others the gradient tiles in order.
+// run of X words, the others the gradient tiles, both from the end: the
+// statistics read the inputs from the beginning, so the end is what the
+// last-level cache still holds of larger ones.
 template <int MODE, int K, int H2, bool VEC>
 __global__ __launch_bounds__(256) void quant_conv_kernel(QuantParams pg, PixelQParams px, ConvWQParams pw, int64_t nbw,
                                                          int64_t nbx, int64_t period, int64_t ctg) {
@@ -1467,17 +1507,18 @@ __global__ __launch_bounds__(256) void quant_conv_kernel(QuantParams pg, PixelQP
   }
   b -= nbw;
   if (b % period == period - 1 && b / period < nbx) {
-    quant_pixels(px, b / period);
+    quant_pixels(px, nbx - 1 - b / period);
   } else {
     const int64_t before = (b + 1) / period < nbx ? (b + 1) / period : nbx;
-    const int64_t t = b - before;
+    const int64_t t = (int64_t)gridDim.x - nbw - nbx - 1 - (b - before);
     quant_tile<MODE, K, H2, VEC, false>(pg, t % ctg, t / ctg);
   }
 }
 
 template <int MODE, int K, int H2>
-static hipError_t launch_quant_conv_k(const QuantParams& pg, const PixelQParams& px, const ConvWQParams& pw,
-                                      hipStream_t s) {
+static hipError_t launch_quant_conv_k(QuantParams pg, PixelQParams px, const ConvWQParams& pw, hipStream_t s) {
+  // (the output words of X stand for its floats: one word per four of them)
+  pg.nt = px.nt = quant_nt(pg.rows * pg.cols + 4 * px.words);
   const int64_t ctg = col_tiles(pg), nbg = ctg * slot_tiles(pg);
   const int64_t nbx = (px.words + PIXQ_WORDS - 1) / PIXQ_WORDS;
   const int64_t nbw = pw.w ? (int64_t)pw.taps * ((pw.c + 15) / 16) : 0;

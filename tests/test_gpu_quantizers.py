@@ -130,3 +130,15 @@ def test_determinism():
     assert torch.equal(a["q"], b["q"]) and torch.equal(a["perm"], b["perm"])
     c = f.fqt_quantize_bhq(x, 5, 64, seed=8, stream=1)
     assert not torch.equal(a["q"], c["q"])
+
+
+@pytest.mark.parametrize("rows,cols", [(6399, 4096), (6400, 4096), (4099, 6400), (6400, 4099)])
+def test_large_inputs_streamed(rows, cols):
+    # inputs of 100 MiB and more are read nontemporally (whole float4 rows only): both sides of
+    # the line, a partial last slot tile, and unaligned rows, which have no such loads
+    f = fqt()
+    x = heavy(rows, rows, cols)
+    ref = Q.quantize_psq(x, 5, seed=3, stream=1)
+    out = f.fqt_quantize_psq(dev(x), 5, seed=3, stream=1, code_sum=True)
+    assert (host(out["q"]) == offset(ref)).all()
+    np.testing.assert_array_equal(host(out["code_sum"]), offset(ref).astype(np.int64).sum(axis=1))
