@@ -88,14 +88,20 @@ __device__ void appd_prefix(const float* rmin, const float* rmax, int64_t rows, 
     __syncthreads();
     if (t == 0) {
       // positions past n add zero, and are not stored
-      for (int i = 0; i < n; i += 16) {
-        float m[16];
-        double q[16];
+      // (the next 16 are read before the chain waits for its own)
+      float m[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) m[u] = sm[i + u];
+      for (int u = 0; u < 16; ++u) m[u] = sm[u];
+      for (int i = 0; i < n; i += 16) {
+        double d[16], q[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) d[u] = (double)m[u];
+        const int nx = i + 16 < APPD_CH ? i + 16 : i;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) m[u] = sm[nx + u];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
-          P = P + (double)m[u];
+          P = P + d[u];
           q[u] = P;
         }
 #pragma unroll
@@ -133,7 +139,7 @@ __device__ __forceinline__ int64_t appd_cum(const double* P, int64_t N, int64_t 
   if (j >= G) return small;
   const double S = P[G];
   const double q = S > 0.0 ? ((double)small * P[j]) / S : (double)(small * j) / (double)G;
-  const int64_t c = (int64_t)floor(q + 0.5);
+  const int64_t c = (int32_t)floor(q + 0.5);  // at most N - G < 2^31
   return c < small ? c : small;
 }
 
@@ -151,32 +157,48 @@ __device__ __forceinline__ double appd_term(const AppdWs& w, int64_t G, int64_t 
   return group_term(s1, s2, n + 1);
 }
 
-// One wave per G (four per block, the largest G first): 64 groups' terms
-// at a time in parallel, then added to the total one at a time in group
-// order (float64).  The terms meet in LDS, where every lane reads them as
-// broadcasts and runs the same chain of additions: the chain, not the term
-// arithmetic, bounds the kernel (2048 rows: 145 us with one cross-lane
-// permute per term).  Terms past G are zero, and adding +0 to a total that is
+// One block per G (the largest first): four waves compute a round of terms, 63
+// each (lane l holds c_i of group i and takes c_(i+1) from lane l + 1; the last
+// lane's group is the next wave's first), into one of two LDS buffers, while the
+// fifth adds the previous round's to the total one at a time in group order
+// (float64; every lane reads them as broadcasts and runs the same chain).  The
+// latency of the largest G's terms and chain bounds the kernel: with one wave
+// per G, terms and chain by turns, 2048 rows took 54 us (2048 x 1024 -> 1024
+// layer with adaptive groups: 183.6 -> 158.0 us, with the prefix sums' reads
+// ahead of the chain).  Terms past G are zero, and adding +0 to a total that is
 // never -0 changes nothing.
-__global__ __launch_bounds__(256) void appd_objective_kernel(int64_t rows, int B, AppdWs w, double* obj) {
-  __shared__ __attribute__((aligned(16))) double sterm[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t id = (int64_t)blockIdx.x * 4 + wave;
-  if (id >= rows) return;
-  const int64_t G = rows - id;
-  double total = 0.0;
-  for (int64_t i0 = 0; i0 < G; i0 += 64) {
-    const int64_t i = i0 + lane;
-    double t = 0.0;
-    if (i < G) t = appd_term(w, G, i, appd_cum(w.P, rows, G, i), appd_cum(w.P, rows, G, i + 1), B);
-    sterm[wave][lane] = t;
-    __builtin_amdgcn_wave_barrier();
+constexpr int OBJ_WAVES = 4, OBJ_TERMS = 63 * OBJ_WAVES;
+__global__ __launch_bounds__(64 * (OBJ_WAVES + 1)) void appd_objective_kernel(int64_t rows, int B, AppdWs w,
+                                                                              double* obj) {
+  __shared__ __attribute__((aligned(16))) double sterm[2][OBJ_TERMS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t id = blockIdx.x; id < rows; id += gridDim.x) {
+    const int64_t G = rows - id;
+    const int64_t rounds = (G + OBJ_TERMS - 1) / OBJ_TERMS;
+    double total = 0.0;
+    for (int64_t k = 0; k <= rounds; ++k) {
+      if (wave < OBJ_WAVES) {
+        const int64_t i = k * OBJ_TERMS + 63 * wave + lane;
+        if (k < rounds && i - lane < G) {
+          const int c0 = (int)appd_cum(w.P, rows, G, i < G ? i : G);
+          const int c1 = __shfl_down(c0, 1);
+          if (lane < 63) sterm[k & 1][63 * wave + lane] = i < G ? appd_term(w, G, i, c0, c1, B) : 0.0;
+        } else if (lane < 63) {
+          sterm[k & 1][63 * wave + lane] = 0.0;
+        }
+      } else if (k > 0) {
+        const double* q = sterm[(k - 1) & 1];
+        for (int l0 = 0; l0 < OBJ_TERMS; l0 += 84) {
 #pragma unroll
-    for (int l = 0; l < 64; ++l) total = total + sterm[wave][l];
-    __builtin_amdgcn_wave_barrier();
+          for (int l = 0; l < 84; ++l) total = total + q[l0 + l];
+        }
+      }
+      __syncthreads();
+    }
+    if (wave == OBJ_WAVES && lane == 0) obj[G - 1] = total;
   }
-  if (lane == 0) obj[G - 1] = total;
 }
+static_assert(OBJ_TERMS % 84 == 0, "whole runs of the chain");
 
 // Least objective over G = 1..rows, ties to the smaller G (one block).
 __global__ __launch_bounds__(1024) void appd_argmin_kernel(int64_t rows, const double* obj, int32_t* G_out) {
@@ -282,7 +304,7 @@ hipError_t launch_appd_search(const float* rmin, const float* rmax, int64_t rows
   if (e != hipSuccess) return e;
   const int B = (1 << bits) - 1;
   double* obj = obj_out ? obj_out : w.obj;
-  hipLaunchKernelGGL(appd_objective_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, rows, B, w, obj);
+  hipLaunchKernelGGL(appd_objective_kernel, dim3((unsigned)(rows < (1 << 20) ? rows : 1 << 20)), dim3(64 * (OBJ_WAVES + 1)), 0, s, rows, B, w, obj);
   hipLaunchKernelGGL(appd_argmin_kernel, dim3(1), dim3(1024), 0, s, rows, obj, num_groups ? num_groups : w.G);
   return hipGetLastError();
 }
