@@ -88,11 +88,13 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t id, int64_t ntiles) {
 // 8 tile columns wide, keep their patch).
 constexpr int TILE_GM = 4;
 __device__ __forceinline__ void tile_mn(int64_t tile, int64_t tiles_m, int64_t tiles_n, int64_t& m, int64_t& n) {
-  const int64_t group = tile / (TILE_GM * tiles_n), first = group * TILE_GM;
-  const int64_t rem = tile - first * tiles_n;
-  const int64_t rows = tiles_m - first < TILE_GM ? tiles_m - first : TILE_GM;
-  n = rem / rows;
-  m = first + (rem - n * rows);
+  // at most 2^31 - 1 tiles (checked at launch): 32-bit divisions
+  const uint32_t t = (uint32_t)tile, tn = (uint32_t)tiles_n, per = TILE_GM * tn;
+  const uint32_t first = t / per * TILE_GM, rem = t - first * tn;
+  const uint32_t left = (uint32_t)tiles_m - first, rows = left < TILE_GM ? left : TILE_GM;
+  const uint32_t c = rem / rows;
+  n = c;
+  m = first + (rem - c * rows);
 }
 
 // The K loops.  The fast one (dma_mainloop below) requires 16-byte aligned
