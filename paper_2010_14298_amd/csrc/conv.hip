@@ -25,7 +25,8 @@
 // (register-staged gather through LDS, float64 epilogue through LDS, two sum
 // kernels of their own): 3x3 64ch 56x56 b128 BHQ 106 -> 62 us, 3x3 s2 128ch
 // 56x56 b256 BHQ 287 -> 176 us, 1x1 1024 -> 256 14x14 b256 PSQ 56 -> 49 us,
-// 3x3 256ch 14x14 b32 PSQ 43 -> 42 us.  Kept back: 32 channels per wave, for
+// 3x3 256ch 14x14 b32 PSQ 43 -> 42 us; with nontemporal output stores and the
+// panel straight to LDS 54, 155, 42 and 31 us.  Kept back: 32 channels per wave, for
 // twice the waves (spills, 174 us on the first); fragment loads three steps
 // ahead (84 us); four-byte stores, one per fragment (72 us).
 #include "gemm_core.h"
