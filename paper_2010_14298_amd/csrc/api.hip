@@ -505,11 +505,11 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
     w.counters = c.take<int32_t>(w.ncounters);
   } else {
     p.part = c.take<int32_t>(parts);
-    w.ncounters = 4 + p.Np + howo * g.o;
+    w.ncounters = 4 + 2 * p.Np + howo * g.o;
     w.counters = c.take<int32_t>(w.ncounters);
-    p.sumB = w.counters ? w.counters + 4 : nullptr;
-    p.qs = w.counters ? w.counters + 4 + p.Np : nullptr;
-    p.sumA = c.take<int32_t>(taps * g.o);
+    p.sumB = w.counters ? reinterpret_cast<int64_t*>(w.counters + 4) : nullptr;
+    p.qs = w.counters ? w.counters + 4 + 2 * p.Np : nullptr;
+    p.sumA = c.take<int64_t>(taps * g.o);
   }
   return w;
 }

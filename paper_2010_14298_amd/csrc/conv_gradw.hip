@@ -330,7 +330,9 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
   }
   __syncthreads();
 
-  // ---- column sums: the two lane halves hold different pixels of a column
+  // ---- column sums: the two lane halves hold different pixels of a column.  A
+  // split's (at most 65536 pixels) are exact in 32 bits; over the splits they
+  // are added in 64, which a tensor of 2^24 pixels needs.
   if (colsum) {
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
@@ -341,7 +343,8 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
         if (lane < 32 && col < p.Np) p.sumBd[((int64_t)split * 2 + wk) * p.Np + col] = w;
       } else {
         const int c = csum[f] + __shfl_xor(csum[f], 32);
-        if (lane < 32 && col < p.Np && c != 0) atomicAdd(p.sumB + col, c);
+        if (lane < 32 && col < p.Np && c != 0)
+          atomicAdd(reinterpret_cast<unsigned long long*>(p.sumB) + col, (unsigned long long)(int64_t)c);
       }
     }
   }
@@ -403,8 +406,9 @@ __device__ __forceinline__ void gradw_tap_range(int r, int stride, int pad, int 
 // tap's valid pixels (a rectangle).  A block takes one tap and 8 channels, its
 // 128 pixel lanes walk the rectangle, eight loads in flight (indices past the
 // end are clamped, their values dropped), and meet in LDS in a fixed order.
-template <typename T>
-__device__ __forceinline__ void gradw_tapsum(const ConvGeom& g, int64_t block, const T* qs, T* sumA) {
+// Sum: the 32-bit sums over the samples add up in 64 bits.
+template <typename T, typename Sum>
+__device__ __forceinline__ void gradw_tapsum(const ConvGeom& g, int64_t block, const T* qs, Sum* sumA) {
   constexpr int PL = 128;
   const int ob = (g.o + 7) / 8;
   const int tap = (int)(block / ob), o0 = 8 * (int)(block % ob);
@@ -414,7 +418,7 @@ __device__ __forceinline__ void gradw_tapsum(const ConvGeom& g, int64_t block, c
   gradw_tap_range(tap % g.kw, g.stride, g.pad, g.w, g.wo, xlo, xhi);
   const int wx = xhi - xlo, cnt = (yhi - ylo) * wx;
   const T* q = qs + o0 + c;  // o is a multiple of 16
-  T sum = 0;
+  Sum sum = 0;
   for (int i0 = pl; i0 < cnt; i0 += 8 * PL) {
     T v[8];
 #pragma unroll
@@ -427,7 +431,7 @@ __device__ __forceinline__ void gradw_tapsum(const ConvGeom& g, int64_t block, c
     for (int u = 0; u < 8; ++u)
       if (i0 + u * PL < cnt) sum += v[u];
   }
-  __shared__ T sp[PL][8];
+  __shared__ Sum sp[PL][8];
   sp[pl][c] = sum;
   for (int h = PL / 2; h > 0; h >>= 1) {
     __syncthreads();
@@ -468,14 +472,14 @@ __device__ __forceinline__ void gradw_sg(const ConvGeom& g, int64_t block, const
 
 // The sums both contractions need, in one launch: blocks [0, nsg) the row sums
 // of Q_b2, then the tap sums of Q_b1, then (per-sample Q_b1) the zero-point sum.
-template <typename T>
+template <typename T, typename Sum>
 __global__ __launch_bounds__(1024) void conv_sums_kernel(ConvGeom g, ConvGradwParams p, int64_t nsg, int64_t ntap,
-                                                         const int8_t* q2, int32_t* sg, const T* qs, T* sumA) {
+                                                         const int8_t* q2, int32_t* sg, const T* qs, Sum* sumA) {
   const int64_t b = blockIdx.x;
   if (b < nsg)
     gradw_sg(g, b, q2, sg);
   else if (b < nsg + ntap)
-    gradw_tapsum<T>(g, b - nsg, qs, sumA);
+    gradw_tapsum<T, Sum>(g, b - nsg, qs, sumA);
   else
     gradw_zsum(p, g.n);
 }
@@ -623,10 +627,10 @@ hipError_t launch_conv_sums(const ConvGradwParams& p, const ConvGeom& g, bool ps
     const int64_t D4 = (int64_t)g.ho * g.wo * g.o / 4;
     if ((D4 + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipLaunchKernelGGL(conv_wsum_kernel, dim3((unsigned)((D4 + 255) / 256)), dim3(256), 0, s, g, p.q1, p.scaleA, p.qsd);
-    hipLaunchKernelGGL(conv_sums_kernel<double>, dim3((unsigned)blocks), dim3(1024), 0, s, g, p, nsg, ntap, q2, sg,
+    hipLaunchKernelGGL((conv_sums_kernel<double, double>), dim3((unsigned)blocks), dim3(1024), 0, s, g, p, nsg, ntap, q2, sg,
                        (const double*)p.qsd, p.sumAd);
   } else {
-    hipLaunchKernelGGL(conv_sums_kernel<int32_t>, dim3((unsigned)blocks), dim3(1024), 0, s, g, p, nsg, ntap, q2, sg,
+    hipLaunchKernelGGL((conv_sums_kernel<int32_t, int64_t>), dim3((unsigned)blocks), dim3(1024), 0, s, g, p, nsg, ntap, q2, sg,
                        (const int32_t*)p.qs, p.sumA);
   }
   return hipGetLastError();

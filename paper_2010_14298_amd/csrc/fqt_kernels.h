@@ -364,9 +364,9 @@ struct ConvGradwParams {
   int64_t per_split;  // pixels per split (per-sample Q_b1: samples)
   int splits;
   int32_t* part;      // [splits][o][Np]
-  int32_t* sumB;      // [Np] X code sums over each column's valid pixels (cleared before)
-  int32_t* qs;        // [ho wo][o] Q_b1 code sums over the samples
-  int32_t* sumA;      // [tap][o] ... over the tap's valid pixels
+  int64_t* sumB;      // [Np] X code sums over each column's valid pixels (cleared before)
+  int32_t* qs;        // [ho wo][o] Q_b1 code sums over the samples (cleared before)
+  int64_t* sumA;      // [tap][o] ... over the tap's valid pixels
   // per-sample Q_b1: the same in float64, weighted by 1 / s_n (sumB: by z_n + half / s_n)
   double* partd;
   double* sumBd;      // [splits][2][Np]

@@ -64,3 +64,23 @@ def test_conv_grad_w_layouts(case, qb_w):
             assert err(gW.cpu().numpy(), r["grad_W64"]) <= 1e-5
             if grad:
                 assert err(gX.cpu().numpy(), r["grad_X64"]) <= 1e-5
+
+
+@pytest.mark.parametrize("c", [1, 16])
+def test_zero_point_sums_beyond_32_bits(c):
+    # 257 * 256 * 256 pixels, nearly all of them at the lowest code (-128) on both sides: the code
+    # sums over the pixels pass -2^31.  Values of 0 and 1 are whole codes, so nothing is rounded and
+    # the gradient is the number of pixels where both are 1.
+    from paper_2010_14298_amd import fqt as f
+    n, h, o = 257, 256, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(c)
+    one = (torch.rand((n, h, h, 1), generator=gen, device="cuda") < 5e-4).float()
+    assert 128 * (one.numel() - 2 * int(one.sum())) > 1 << 31
+    X, G = one.expand(-1, -1, -1, c).contiguous(), one.expand(-1, -1, -1, o).contiguous()
+    W = torch.ones((o, 1, 1, c), device="cuda")
+    gW, _, ws = f.fqt_conv_backward_im2col(X, W, G, 1, 0, qb_x=("ptq", 8, 0), qb_w=("ptq", 8, 0), seed=1,
+                                           input_grad=False)
+    assert f.fqt_workspace_status(ws) == 0
+    # one float32 rounding, and 2^-52 of the zero-point term (a quarter of the pixels) a few times over
+    torch.testing.assert_close(gW, torch.full_like(gW, float(one.sum())), rtol=1e-6, atol=0)
