@@ -472,6 +472,11 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   w.xq = c.take<int8_t>(w.xbytes);
   w.wq_t = c.take<int8_t>((int64_t)g.c * taps * g.o);
   w.q2 = c.take<int8_t>(N * howo * g.o);
+  // right after q2: grad_X reaches the 16 zero bytes from it by a 32-bit offset
+  // in 16-byte steps, which the general plan's rows in between could exceed
+  const int64_t Np = conv_gradw_cols(g);
+  w.ncounters = psq1 ? 4 : 4 + 2 * Np + howo * g.o;
+  w.counters = c.take<int32_t>(w.ncounters);
   w.q1 = c.take<int8_t>(N * howo * g.o);
   w.swq = c.take<int32_t>(taps * g.c);
   w.sg = c.take<int32_t>(N * howo);
@@ -492,7 +497,7 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   ConvGradwParams& p = w.gw;
   p.q1 = w.q1;
   p.xq = w.xq;
-  p.Np = conv_gradw_cols(g);
+  p.Np = Np;
   conv_gradw_splits(g, psq1, p.per_split, p.splits);
   const int64_t parts = (int64_t)p.splits * g.o * p.Np;
   if (psq1) {
@@ -501,14 +506,10 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
     p.qsd = c.take<double>(howo * g.o);
     p.sumAd = c.take<double>(taps * g.o);
     p.zsum = c.take<double>(1);
-    w.ncounters = 4;
-    w.counters = c.take<int32_t>(w.ncounters);
   } else {
     p.part = c.take<int32_t>(parts);
-    w.ncounters = 4 + 2 * p.Np + howo * g.o;
-    w.counters = c.take<int32_t>(w.ncounters);
     p.sumB = w.counters ? reinterpret_cast<int64_t*>(w.counters + 4) : nullptr;
-    p.qs = w.counters ? w.counters + 4 + 2 * p.Np : nullptr;
+    p.qs = w.counters ? w.counters + 4 + 2 * Np : nullptr;
     p.sumA = c.take<int64_t>(taps * g.o);
   }
   return w;

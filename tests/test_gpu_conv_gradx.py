@@ -63,3 +63,21 @@ def test_group_spans(k, n):
 @pytest.mark.parametrize("n,qb_x", [(6, ("psq", 8, 0)), (70, ("bhq", 5, 64))])
 def test_panels(geo, n, qb_x):
     check(sum(geo), n, *geo, qb_x)
+
+
+def test_large_general_plan_workspace():
+    # the general plan's float64 rows alone take 64 GiB of the workspace; gradient and weights of 0
+    # and 1 are whole codes, so grad_X is their product exactly
+    from paper_2010_14298_amd import fqt as f
+    h, w, c, o = 255, 257, 8208, 16
+    assert 8 * 16 * h * w * c > 1 << 36
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    G, W = (torch.rand(s, generator=gen, device="cuda").round() for s in ((1, h, w, o), (o, 1, 1, c)))
+    X = torch.zeros((1, h, w, c), device="cuda")
+    gW, gX, ws = f.fqt_conv_backward_im2col(X, W, G, 1, 0, qb_x=("bhq", 5, 3), seed=1)
+    assert f.fqt_workspace_status(ws) == 0
+    del ws
+    torch.cuda.empty_cache()
+    assert float(gW.abs().max()) == 0.0
+    assert float((gX.view(h * w, c) - G.view(h * w, o) @ W.view(o, c)).abs().max()) <= 16 * 2.0 ** -22
