@@ -906,8 +906,9 @@ __device__ __forceinline__ void quant_tile(const QuantParams& p, int64_t bx, int
   const int64_t nat0 = p.pm_o > 0 ? (c0 / p.pm_o) * rows * p.pm_o + c0 % p.pm_o + slot0 * p.pm_o : slot0 * ldn + c0;
   const int64_t nat_step = p.pm_o > 0 ? p.pm_o : ldn;
   // whole words of natural codes: always with VEC; else rows padded with zero
-  // codes to a pitch of whole words
-  const bool nat_word = VEC || p.ldn > 0;
+  // codes to a pitch of whole words, or whole words by themselves (an unaligned
+  // input of such a width)
+  const bool nat_word = VEC || p.ldn > 0 || ((cols & 3) == 0 && ((uintptr_t)p.q_nat & 3) == 0);
   const bool nat_ok = c0 < (p.ldn > 0 ? p.ldn : cols);
   int32_t rs4[4];                // per-lane partial row sums of the natural codes, 4 rows at a time
   uint32_t tq[4][4], tq2[4][4];  // transposed codes: [column][4 words of 16 slots]; rows past the end stay 0
@@ -1209,23 +1210,27 @@ __global__ __launch_bounds__(256) void quant_tile_kernel(QuantParams p) {
 // per-tensor transposed passes (Q_f(X), Q_theta(W)) in one grid.  Every
 // period-th block (while they last) is an X / W tile, so that those
 // memory-light tiles interleave with the arithmetic-heavy gradient tiles;
-// the other blocks take the gradient tiles in order.
-template <int MODE, int K, int H2, bool VEC>
+// the other blocks take the gradient tiles in order.  Whole float4 rows are
+// each matrix's own affair (VECG, vecx, vecw): an odd width of X and W leaves
+// the gradient its float4 tiles.
+template <int MODE, int K, int H2, bool VECG>
 __global__ __launch_bounds__(256) void quant_fused_kernel(QuantParams pg, QuantParams px, QuantParams pw, int64_t nbx,
                                                           int64_t nbw, int64_t period, int64_t ctg, int64_t ctx,
-                                                          int64_t ctw) {
+                                                          int64_t ctw, bool vecx, bool vecw) {
   const int64_t b = blockIdx.x;
   const int64_t nxw = nbx + nbw;
   if (b % period == period - 1 && b / period < nxw) {
-    const int64_t t = b / period;
-    if (t < nbx)
-      quant_tile<QM_TENSOR, 0, 0, VEC, true>(px, t % ctx, t / ctx);
+    const bool x = b / period < nbx;
+    const int64_t t = b / period - (x ? 0 : nbx), ct = x ? ctx : ctw;
+    const QuantParams& p = x ? px : pw;
+    if (x ? vecx : vecw)
+      quant_tile<QM_TENSOR, 0, 0, true, true>(p, t % ct, t / ct);
     else
-      quant_tile<QM_TENSOR, 0, 0, VEC, true>(pw, (t - nbx) % ctw, (t - nbx) / ctw);
+      quant_tile<QM_TENSOR, 0, 0, false, true>(p, t % ct, t / ct);
   } else {
     const int64_t before = (b + 1) / period < nxw ? (b + 1) / period : nxw;
     const int64_t t = b - before;
-    quant_tile<MODE, K, H2, VEC, false>(pg, t % ctg, t / ctg);
+    quant_tile<MODE, K, H2, VECG, false>(pg, t % ctg, t / ctg);
   }
 }
 
@@ -1259,7 +1264,14 @@ static bool pitch_ok(const QuantParams& p) {
 // with the conv launch's order from the end 462 (the order alone: 475); 3001 x 1024 -> 4096 (78 MB) 121.0 / 117.7.
 static int quant_nt(int64_t floats) { return floats * 4 >= (int64_t)100 << 20; }
 
-template <int MODE, int K, bool VEC>
+// Rows of whole float4s: one 16-byte load and one Philox block per lane and
+// row; else the tiles with unaligned loads and up to two blocks.  Chosen for
+// each matrix of a launch: with one choice for all, an odd d_in took the
+// gradient off its float4 tiles (layers of 2048 x 1023 -> 1024 64.2 us against
+// 61.1, 4096 x 510 -> 512 in blocks of 48 107.5 against 101.4).
+static bool quant_vec(const QuantParams& p) { return (p.cols % 4 == 0) && (((uintptr_t)p.x & 15) == 0); }
+
+template <int MODE, int K, int H2, bool VECG>
 static hipError_t launch_quant_fused_v(QuantParams pg, QuantParams px, QuantParams pw, hipStream_t s) {
   pg.nt = px.nt = pw.nt = quant_nt(pg.rows * pg.cols + px.rows * px.cols + pw.rows * pw.cols);
   if (!pitch_ok(pg) || !pitch_ok(px) || !pitch_ok(pw)) return hipErrorInvalidValue;
@@ -1270,23 +1282,19 @@ static hipError_t launch_quant_fused_v(QuantParams pg, QuantParams px, QuantPara
   const int64_t nb = nbg + nbx + nbw;
   if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
   const int64_t period = nb / (nbx + nbw);
-  if (pg.shift2)
-    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 2, VEC>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
-                       period, ctg, ctx, ctw);
-  else
-    hipLaunchKernelGGL((quant_fused_kernel<MODE, K, 1, VEC>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
-                       period, ctg, ctx, ctw);
+  hipLaunchKernelGGL((quant_fused_kernel<MODE, K, H2, VECG>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
+                     period, ctg, ctx, ctw, quant_vec(px), quant_vec(pw));
   return hipGetLastError();
 }
 
-// Rows of whole float4s (and one Philox block per lane and row), or the
-// general tiles when any of the three matrices has none.
-static bool quant_vec(const QuantParams& p) { return (p.cols % 4 == 0) && (((uintptr_t)p.x & 15) == 0); }
 template <int MODE, int K>
 static hipError_t launch_quant_fused_k(const QuantParams& pg, const QuantParams& px, const QuantParams& pw,
                                        hipStream_t s) {
-  if (quant_vec(pg) && quant_vec(px) && quant_vec(pw)) return launch_quant_fused_v<MODE, K, true>(pg, px, pw, s);
-  return launch_quant_fused_v<MODE, K, false>(pg, px, pw, s);
+  if (quant_vec(pg))
+    return pg.shift2 ? launch_quant_fused_v<MODE, K, 2, true>(pg, px, pw, s)
+                     : launch_quant_fused_v<MODE, K, 1, true>(pg, px, pw, s);
+  return pg.shift2 ? launch_quant_fused_v<MODE, K, 2, false>(pg, px, pw, s)
+                   : launch_quant_fused_v<MODE, K, 1, false>(pg, px, pw, s);
 }
 
 template <int MODE, int K>

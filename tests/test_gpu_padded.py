@@ -80,3 +80,31 @@ def test_codes_of_unaligned_rows(rows, cols, shift):
     codes = (ref["code"] - Q.offset(5)).astype(np.int8)
     np.testing.assert_array_equal(host(out["q"]), codes)
     np.testing.assert_array_equal(host(out["code_sum"]), codes.astype(np.int32).sum(axis=1))
+
+
+@pytest.mark.parametrize("shape", [(130, 255, 128), (64, 33, 256), (129, 256, 384)])
+@pytest.mark.parametrize("shifts", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 0)])
+@pytest.mark.parametrize("qb_x,qb_w", [(("ptq", 8, 0), ("ptq", 8, 0)), (("psq", 4, 0), ("shift", 4, 0)),
+                                       (("bhq", 5, 64), ("ptq", 8, 0)), (("bhq", 5, 48), ("ptq", 8, 0))])
+def test_linear_rows_of_each_matrix(shape, shifts, qb_x, qb_w):
+    # odd widths of X and W beside a gradient of whole float4 rows and no padding (d_out % 128 == 0),
+    # and one unaligned matrix beside aligned ones: each matrix has its own kind of tile
+    N, d_in, d_out = shape
+    X, W, G = synth.linear_small(seed=sum(shape), n=N, d_in=d_in, d_out=d_out)
+    r = BW.linear_backward(X, W, G, qb_x=qb_x, qb_w=qb_w, seed=9)
+    f = fqt()
+    gW, gX, ws = f.fqt_linear_backward(*(dev(t, s) for t, s in zip((X, W, G), shifts)), qb_x=qb_x, qb_w=qb_w, seed=9)
+    assert f.fqt_workspace_status(ws) == 0
+    assert rownorm_err(host(gW), r["grad_W64"]) <= REL_TOL
+    assert rownorm_err(host(gX), r["grad_X64"]) <= REL_TOL
+
+
+@pytest.mark.parametrize("rows,cols", [(65, 256), (64, 260)])
+def test_codes_of_unaligned_whole_words(rows, cols):
+    rng = np.random.default_rng(rows + cols)
+    x = (rng.standard_normal((rows, cols)) * rng.lognormal(0, 2, (rows, 1))).astype(np.float32)
+    f = fqt()
+    out = f.fqt_quantize_psq(dev(x, 1), 5, seed=3, code_sum=True)
+    codes = (Q.quantize_psq(x, 5, seed=3, stream=0)["code"] - Q.offset(5)).astype(np.int8)
+    np.testing.assert_array_equal(host(out["q"]), codes)
+    np.testing.assert_array_equal(host(out["code_sum"]), codes.astype(np.int32).sum(axis=1))
