@@ -87,7 +87,7 @@ __device__ __forceinline__ bool tap_hits(const ConvGeom& g, int iy, int ix, int 
 // whose pixel the tap misses takes no MFMA.  Otherwise each lane group looks its list
 // position up in LDS.
 // ONE: the unit's rows share their pixel.
-template <int EPI, int KE, bool UNI, bool ONE>
+template <int EPI, int KE, bool UNI, bool ONE, bool NT>
 __global__ __launch_bounds__(512, 2) void conv_gradx_kernel(GemmParams p, ConvGeom g, ConvXTile t, const int8_t* q2,
                                                           const int32_t* sg, const int32_t* swq) {
   extern __shared__ __attribute__((aligned(16))) int8_t cx_lds[];
@@ -562,11 +562,11 @@ __global__ __launch_bounds__(512, 2) void conv_gradx_kernel(GemmParams p, ConvGe
           o[j] = (float)v;
         }
         if (vec) {
-          stream_store4(dst, make_float4(o[0], o[1], o[2], o[3]));
+          out_store4<NT>(dst, make_float4(o[0], o[1], o[2], o[3]));
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            if (col + j < g.c) stream_store(dst + j, o[j]);
+            if (col + j < g.c) out_store<NT>(dst + j, o[j]);
         }
       }
     }
@@ -580,9 +580,9 @@ __global__ __launch_bounds__(512, 2) void conv_gradx_kernel(GemmParams p, ConvGe
 constexpr int CX_LDS = 160 * 1024;  // LDS of a CU
 constexpr int CX_CUS = 256;
 
-template <int EPI, int KE>
-static hipError_t launch_conv_gradx_t(const GemmParams& p, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,
-                                      const int32_t* sg, const int32_t* swq, hipStream_t s) {
+template <int EPI, int KE, bool NT>
+static hipError_t launch_conv_gradx_nt(const GemmParams& p, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,
+                                       const int32_t* sg, const int32_t* swq, hipStream_t s) {
   const int taps = g.kh * g.kw;
   const int64_t M = (int64_t)g.h * g.w * g.npad;
   if (M > 0x7FFFFFFF - 64 || p.M != M || (g.npad != 16 && g.npad != 32 && g.npad % 64 != 0) || g.npad < g.n ||
@@ -636,7 +636,7 @@ static hipError_t launch_conv_gradx_t(const GemmParams& p, const ConvGeom& g, co
   const bool uni = g.o % 64 == 0 && t.cpc % 64 == 0 && (int64_t)g.n * g.o < ((int64_t)1 << 32);
   const bool one = g.npad >= 64;
 #define FQT_GRADX(UNI, ONE)                                                                                            \
-  hipLaunchKernelGGL((conv_gradx_kernel<EPI, KE, UNI, ONE>), dim3((unsigned)blocks), dim3((unsigned)(64 * waves)),     \
+  hipLaunchKernelGGL((conv_gradx_kernel<EPI, KE, UNI, ONE, NT>), dim3((unsigned)blocks), dim3((unsigned)(64 * waves)),     \
                      (size_t)lds, s, p, g, t, q2, sg, swq)
   if constexpr (KE < 64) {
     if (uni && one)
@@ -654,6 +654,13 @@ static hipError_t launch_conv_gradx_t(const GemmParams& p, const ConvGeom& g, co
   }
 #undef FQT_GRADX
   return hipGetLastError();
+}
+
+template <int EPI, int KE>
+static hipError_t launch_conv_gradx_t(const GemmParams& p, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,
+                                      const int32_t* sg, const int32_t* swq, hipStream_t s) {
+  return stream_rows(p.out, p.ldo, STREAM_CONV) ? launch_conv_gradx_nt<EPI, KE, true>(p, g, q2, zero16, sg, swq, s)
+                                      : launch_conv_gradx_nt<EPI, KE, false>(p, g, q2, zero16, sg, swq, s);
 }
 
 hipError_t launch_conv_gradx(const GemmParams& p, int epi, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,

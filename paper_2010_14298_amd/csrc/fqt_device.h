@@ -239,18 +239,27 @@ __device__ __forceinline__ double group_term(float s1, float s2, int64_t k) {
 }
 
 // Stores of a layer's float32 outputs, a write stream that nothing in the
-// launch reads again: nontemporal, so that they neither push the operand codes
-// out of L2 nor leave the caches full of dirty lines for the next launch to
-// write back.  Against plain stores: forward 8192 x 1024 -> 4096 119.3 -> 99.7
-// us, FFN layer 213.4 -> 202.5, 3x3 s2 128ch 56x56 b256 528 -> 478, 3x3 64ch
-// 56x56 b128 262 -> 247, 3001 x 1024 -> 4096 123.6 -> 117.0; a following layer
-// that reads the outputs gains too (3-layer MLP 1.530 -> 1.488 ms a step).  A
-// choice between both kinds by the output's size doubles the epilogues' code
-// and slows the smallest layers (128 x 256 -> 256 37.1 -> 39.6 us).
+// launch reads again.  NT: nontemporal, so that they neither push the operand
+// codes out of L2 nor leave the caches full of dirty lines for the next launch
+// to write back (forward 8192 x 1024 -> 4096 119.3 -> 99.7 us against ordinary
+// stores, FFN layer 213.4 -> 202.5, 3x3 s2 128ch 56x56 b256 528 -> 478; a
+// following layer that reads the outputs gains too).  Chosen at launch by
+// stream_rows, each kind a kernel of its own: a choice inside the epilogue
+// doubles its code and slows the smallest layers.
 typedef float v4f __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void stream_store(float* p, float v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void stream_store4(float* p, const float4& f) {
-  __builtin_nontemporal_store(v4f{f.x, f.y, f.z, f.w}, reinterpret_cast<v4f*>(p));
+template <bool NT>
+__device__ __forceinline__ void out_store(float* p, float v) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+template <bool NT>
+__device__ __forceinline__ void out_store4(float* p, const float4& f) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v4f{f.x, f.y, f.z, f.w}, reinterpret_cast<v4f*>(p));
+  else
+    *reinterpret_cast<float4*>(p) = f;
 }
 // Keeps the two sides of a branch apart: the compiler merges an ordinary and a
 // nontemporal access to one ordinary access.

@@ -303,6 +303,25 @@ hipError_t launch_gemm(const GemmParams& p, int epi, hipStream_t s);
 // per-tensor epilogue (EPI_TENSOR) into p.out.
 hipError_t launch_splitk_reduce(const GemmParams& p, int64_t* out64, int epi, hipStream_t s);
 
+// Whether a launch stores its float32 output (rows of ldo) nontemporally: rows
+// in whole units of `unit` floats.  Ordinary stores that leave part of a cache
+// line meet in L2 with those that fill it; nontemporal ones go out as they are,
+// and a part of a line costs memory a read as well.  The unit lies where that
+// outweighs the gain, nontemporal / ordinary in us:
+// - STREAM_TENSOR, one float per lane (runs of 128 bytes): whole lines.  Forward
+//   8192 x 512 -> 4096 75 / 77, -> 4080 (64-byte rows) 97 / 79, -> 4095 95 / 78.
+// - STREAM_ROW, four floats per lane (runs of 256 bytes): half lines.  Layer
+//   8192 x 1008 -> 512 97.7 / 98.4, 8192 x 1020 -> 512 104 / 99, 8192 x 4095 ->
+//   128 343 / 186.
+// - STREAM_CONV, the same from a conv, whose time the stores bound more: the
+//   16 bytes of a lane.  56x56 b128: 3x3 80ch 264 / 282, 84ch 317 / 332, 1x1
+//   104ch 310 / 324; only wide odd pitches lose (1x1 196ch 469 / 439).  Without
+//   whole 16 bytes the stores are single floats: 3x3 83ch 470 / 320.
+enum StreamUnit { STREAM_TENSOR = 32, STREAM_ROW = 16, STREAM_CONV = 4 };
+inline bool stream_rows(const float* out, int64_t ldo, StreamUnit unit) {
+  return ldo % unit == 0 && (uintptr_t)out % (4 * unit) == 0;
+}
+
 // Zero-point term of a contraction over samples whose A rows (samples) carry
 // their own zero points: v[c] = sum_n zeta_n Xt[n, c] (zeta_n = half / s_n +
 // z_n from the finalize), Xt[n, c] = dx q[c, n] + zx (q: [cols, ldq]

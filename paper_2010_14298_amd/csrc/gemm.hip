@@ -41,9 +41,10 @@ struct GroupStage {
 
 // grad_X store; with a mask (the layer input X, for the ReLU that produced
 // it) entries where the mask is not positive are zero.
+template <bool NT>
 __device__ __forceinline__ void store_masked(const GemmParams& p, int64_t idx, double v) {
   const float f = (float)v;
-  stream_store(p.out + idx, (p.mask && !(p.mask[idx] > 0.0f)) ? 0.0f : f);
+  out_store<NT>(p.out + idx, (p.mask && !(p.mask[idx] > 0.0f)) ? 0.0f : f);
 }
 
 template <class C, int EPI>
@@ -53,7 +54,7 @@ struct GemmLdsSize {
   static constexpr int BYTES = (STAGED && EP_BYTES > C::OP_BYTES) ? EP_BYTES : C::OP_BYTES;
 };
 
-template <class C, int EPI, int KG, bool FAST, bool PK = false>
+template <class C, int EPI, int KG, bool FAST, bool PK, bool NT>
 __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(16))) int8_t lds[GemmLdsSize<C, EPI>::BYTES];
   const int tid = threadIdx.x;
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
           const int64_t col = n0 + wn * C::WN + j * 32 + lrow;
           if (col < p.N) {
             const float v = (float)(dAB * (double)acc[i][j][r] + rterm + cterm[j]);
-            stream_store(p.out + row * p.ldo + col, (p.relu && !(v > 0.0f)) ? 0.0f : v);
+            out_store<NT>(p.out + row * p.ldo + col, (p.relu && !(v > 0.0f)) ? 0.0f : v);
           }
         }
       }
@@ -255,11 +256,11 @@ __global__ __launch_bounds__(C::THREADS) void gemm_i8_kernel(GemmParams p) {
             f.z = m.z > 0.0f ? f.z : 0.0f;
             f.w = m.w > 0.0f ? f.w : 0.0f;
           }
-          stream_store4(p.out + idx, f);
+          out_store4<NT>(p.out + idx, f);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (col + e < p.N) store_masked(p, idx + e, v[e]);
+            if (col + e < p.N) store_masked<NT>(p, idx + e, v[e]);
         }
       };
       if constexpr (EPI == EPI_BHQ && KG > 1) {
@@ -461,8 +462,8 @@ int64_t gemm_tiles(int64_t M, int64_t N) {
 // Large tiles when they still give every CU a block; small ones otherwise.
 static bool gemm_use_large(int64_t M, int64_t N) { return gemm_tiles<CfgLarge>(M, N) >= 256; }
 
-template <class C, int EPI, int KG>
-static hipError_t launch_gemm_t(GemmParams p, hipStream_t s) {
+template <class C, int EPI, int KG, bool NT>
+static hipError_t launch_gemm_nt(const GemmParams& p, hipStream_t s) {
   const int64_t tiles = gemm_tiles<C>(p.M, p.N);
   if (tiles > 0x7FFFFFFF || p.splits > 65535) return hipErrorInvalidValue;
   // fast K loop: aligned rows, whole stages per split
@@ -473,16 +474,24 @@ static hipError_t launch_gemm_t(GemmParams p, hipStream_t s) {
   if constexpr (EPI == EPI_ROW || EPI == EPI_BHQ || EPI == EPI_BHQT) {
     if (p.packedA) {
       if (p.K % 16 != 0 || (p.lda & 7) != 0 || ((uintptr_t)p.A & 7) != 0) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, false, true>), grid, dim3(C::THREADS), 0, s, p);
+      hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, false, true, NT>), grid, dim3(C::THREADS), 0, s, p);
       return hipGetLastError();
     }
   }
   if (p.packedA) return hipErrorInvalidValue;
   if (fast)
-    hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, true>), grid, dim3(C::THREADS), 0, s, p);
+    hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, true, false, NT>), grid, dim3(C::THREADS), 0, s, p);
   else
-    hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, false>), grid, dim3(C::THREADS), 0, s, p);
+    hipLaunchKernelGGL((gemm_i8_kernel<C, EPI, KG, false, false, NT>), grid, dim3(C::THREADS), 0, s, p);
   return hipGetLastError();
+}
+
+template <class C, int EPI, int KG>
+static hipError_t launch_gemm_t(const GemmParams& p, hipStream_t s) {
+  if constexpr (EPI != EPI_RAW_I32) {
+    if (stream_rows(p.out, p.ldo, EPI == EPI_TENSOR ? STREAM_TENSOR : STREAM_ROW)) return launch_gemm_nt<C, EPI, KG, true>(p, s);
+  }
+  return launch_gemm_nt<C, EPI, KG, false>(p, s);
 }
 
 template <class C>
