@@ -474,8 +474,8 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   w.q2 = c.take<int8_t>(N * howo * g.o);
   // right after q2: grad_X reaches the 16 zero bytes from it by a 32-bit offset
   // in 16-byte steps, which the general plan's rows in between could exceed
-  const int64_t Np = conv_gradw_cols(g);
-  w.ncounters = psq1 ? 4 : 4 + 2 * Np + howo * g.o;
+  const int64_t nsumB = GRADW_SUMB * conv_gradw_cols(g);
+  w.ncounters = psq1 ? 4 : 4 + 2 * nsumB + howo * g.o;
   w.counters = c.take<int32_t>(w.ncounters);
   w.q1 = c.take<int8_t>(N * howo * g.o);
   w.swq = c.take<int32_t>(taps * g.c);
@@ -497,19 +497,18 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   ConvGradwParams& p = w.gw;
   p.q1 = w.q1;
   p.xq = w.xq;
-  p.Np = Np;
+  p.Np = conv_gradw_cols(g);
   conv_gradw_splits(g, psq1, p.per_split, p.splits);
-  const int64_t parts = (int64_t)p.splits * g.o * p.Np;
+  const int64_t parts = (int64_t)p.splits * (psq1 ? g.o + 2 : g.o) * p.Np;
   if (psq1) {
     p.partd = c.take<double>(parts);
-    p.sumBd = c.take<double>((int64_t)p.splits * 2 * p.Np);
     p.qsd = c.take<double>(howo * g.o);
     p.sumAd = c.take<double>(taps * g.o);
     p.zsum = c.take<double>(1);
   } else {
     p.part = c.take<int32_t>(parts);
     p.sumB = w.counters ? reinterpret_cast<int64_t*>(w.counters + 4) : nullptr;
-    p.qs = w.counters ? w.counters + 4 + 2 * Np : nullptr;
+    p.qs = w.counters ? w.counters + 4 + 2 * nsumB : nullptr;
     p.sumA = c.take<int64_t>(taps * g.o);
   }
   return w;

@@ -332,19 +332,22 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
 
   // ---- column sums: the two lane halves hold different pixels of a column.  A
   // split's (at most 65536 pixels) are exact in 32 bits; over the splits they
-  // are added in 64, which a tensor of 2^24 pixels needs.
+  // are added in 64, which a tensor of 2^24 pixels needs.  Per-sample sums are
+  // float64: kept per split and K half, rows o and o + 1 of its partial sums,
+  // and added in a fixed order.
+  const int64_t prow = (int64_t)split * (PSQ ? g.o + 2 : g.o);
   if (colsum) {
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
       const int col = n0 + 64 * wn + 32 * f + (lane & 31);
       if constexpr (PSQ) {
         const double w = wb[f] + __shfl_xor(wb[f], 32);
-        // [split][K half][Np]
-        if (lane < 32 && col < p.Np) p.sumBd[((int64_t)split * 2 + wk) * p.Np + col] = w;
+        if (lane < 32 && col < p.Np) p.partd[(prow + g.o + wk) * p.Np + col] = w;
       } else {
         const int c = csum[f] + __shfl_xor(csum[f], 32);
         if (lane < 32 && col < p.Np && c != 0)
-          atomicAdd(reinterpret_cast<unsigned long long*>(p.sumB) + col, (unsigned long long)(int64_t)c);
+          atomicAdd(reinterpret_cast<unsigned long long*>(p.sumB) + (split % GRADW_SUMB) * p.Np + col,
+                    (unsigned long long)(int64_t)c);
       }
     }
   }
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
       if (wk == 0)
         each(i, [&](int j, int r, int row, int col) {
           if (row < g.o && col < p.Np)
-            p.partd[((int64_t)split * g.o + row) * p.Np + col] = accd[i][j][r] + sh[(j * 16 + r) * 64 + lane];
+            p.partd[(prow + row) * p.Np + col] = accd[i][j][r] + sh[(j * 16 + r) * 64 + lane];
         });
       __syncthreads();
     }
@@ -387,7 +390,7 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
       for (int i = 0; i < 2; ++i)
         each(i, [&](int j, int r, int row, int col) {
           if (row < g.o && col < p.Np)
-            p.part[((int64_t)split * g.o + row) * p.Np + col] = acc[i][j][r] + sh[((i * 2 + j) * 16 + r) * 64 + lane];
+            p.part[(prow + row) * p.Np + col] = acc[i][j][r] + sh[((i * 2 + j) * 16 + r) * 64 + lane];
         });
   }
 }
@@ -514,33 +517,109 @@ __global__ __launch_bounds__(256) void conv_wsum_kernel(ConvGeom g, const int8_t
 //   per tensor: dA dB acc + dA zB SA[tap][o] + zA dB SB[col] + cnt zA zB
 //   per sample: dB sum_n dA_n acc_n + zB sum_n dA_n SA_n + dB sum_n zA_n SB_n
 //               + zB (valid pixels per sample) sum_n zA_n
-// A block takes 64 outputs; its wave w sums splits w, w + 4, ... with eight
-// loads in flight, and the four wave sums meet in LDS.
+// A block takes 64 columns and W / sl rows of the partial sums: sl waves per
+// row, each over every sl-th split, and all W waves over the parts of the column
+// sums, a batch of loads of each in flight.  The waves' sums meet in LDS and are
+// added in a fixed order.  Loads waiting on each other are all there is to it,
+// so sl is the least that leaves a wave one batch of eight, at most 16, and W =
+// sl, at least 4.  With 64 outputs and four waves per block whatever the number
+// of splits (and the column sums of a per-sample Q_b1 added by one thread each):
+// 3x3 3 -> 32 64x64 b128 (512 splits) 40 us, now 8; the same per sample (128
+// splits) 74, now 8; stem (256) 22, now 7; 3x3 64ch 56x56 b128 (96) 10.5, now
+// 8.8; 3x3 256ch 14x14 b32 per sample (7) 17, now 10.
+constexpr int GR_WAVES = 16, GR_BATCH = 8;
+inline int gradw_log2_split_lanes(int splits) {
+  int l = 0;
+  while ((1 << l) < GR_WAVES && splits > GR_BATCH << l) ++l;
+  return l;
+}
 template <bool PSQ>
-__device__ __forceinline__ void gradw_reduce(const ConvGradwParams& p, const ConvGeom& g, int64_t block) {
+__global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGradwParams p, ConvGeom g, int lsl) {
   using Sum = typename std::conditional<PSQ, double, int64_t>::type;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int taps = g.kh * g.kw, N = taps * g.c;
-  const int64_t MN = (int64_t)g.o * N;
-  const int64_t idx = block * 64 + lane;
-  const int64_t ic = idx < MN ? idx : MN - 1;
-  const int row = (int)(ic / N), col = (int)(ic - (int64_t)row * N);
-  const int tap = col / g.c, ch = col - tap * g.c;
-  const int r = tap / g.kw, s = tap - r * g.kw;
-  const int colp = g.cp == 4 ? 16 * (r * ((g.kw + 3) / 4) + (s >> 2)) + 4 * (s & 3) + ch : tap * g.cp + ch;
-  const int64_t at = (int64_t)row * p.Np + colp, pitch = (int64_t)g.o * p.Np;
-  auto part = [&](int sp) { return PSQ ? (Sum)p.partd[sp * pitch + at] : (Sum)p.part[sp * pitch + at]; };
-  Sum s8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int sp = wave;
-  for (; sp + 28 < p.splits; sp += 32)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int W = blockDim.x >> 6, rows = W >> lsl, sl = 1 << lsl;
+  const int cols = (int)((p.Np + 63) / 64);
+  const int row0 = (int)(blockIdx.x / cols) * rows;  // o is a multiple of 16: whole runs of rows
+  const int colp = (int)(blockIdx.x % cols) * 64 + lane;
+  const int64_t cc = colp < p.Np ? colp : p.Np - 1, pitch = (int64_t)(PSQ ? g.o + 2 : g.o) * p.Np;
+  typedef typename std::conditional<PSQ, double, int>::type Part;
+  typedef typename std::conditional<PSQ, double, int64_t>::type Col;
+  // one batch: entries e0, e0 + step, ... below n (past it: the first, dropped
+  // in the sum, so that the loads issue without branches), entry e being partial
+  // row r of split e, or part e of the column sums
+  auto load = [&](Part (&v)[GR_BATCH], int r, int e0, int step, int n) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s8[u] += part(sp + 4 * u);
-  for (; sp < p.splits; sp += 4) s8[0] += part(sp);
-  __shared__ Sum sw[4][64];
-  sw[wave][lane] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+    for (int u = 0; u < GR_BATCH; ++u) {
+      const int64_t i = (e0 + u * step < n ? e0 + u * step : 0) * pitch + (int64_t)r * p.Np + cc;
+      if constexpr (PSQ)
+        v[u] = p.partd[i];
+      else
+        v[u] = p.part[i];
+    }
+  };
+  constexpr int CB = PSQ ? GR_BATCH : GRADW_SUMB / 4;  // one batch of the copies for four waves
+  auto load_col = [&](Col (&v)[CB], int e0, int step, int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < CB; ++u) {
+      const int e = e0 + u * step < n ? e0 + u * step : 0;
+      if constexpr (PSQ)
+        v[u] = p.partd[(e >> 1) * pitch + (int64_t)(g.o + (e & 1)) * p.Np + cc];
+      else
+        v[u] = p.sumB[e * p.Np + cc];
+    }
+  };
+  auto add = [&](const auto& v, int e0, int step, int n) __attribute__((always_inline)) {
+    Sum sum = 0;
+#pragma unroll
+    for (int u = 0; u < (int)(sizeof(v) / sizeof(v[0])); ++u) sum += e0 + u * step < n ? (Sum)v[u] : (Sum)0;
+    return sum;
+  };
+  const int myrow = row0 + (wave >> lsl), q = wave & (sl - 1), S = p.splits;
+  const int NC = PSQ ? 2 * S : GRADW_SUMB;  // parts of the column sums
+  Part vr[GR_BATCH];
+  Col vc[CB];
+  load(vr, myrow, q, sl, S);
+  load_col(vc, wave, W, NC);
+  // partial column -> tap and channel (none: padding)
+  int r, s, ch;
+  if (g.cp == 4) {
+    const int q4 = (g.kw + 3) / 4, chunk = colp / 16;
+    r = chunk / q4;
+    s = 4 * (chunk - r * q4) + ((colp & 15) >> 2);
+    ch = colp & 3;
+  } else {
+    const int tap = colp / g.cp;
+    ch = colp - tap * g.cp;
+    r = tap / g.kw;
+    s = tap - r * g.kw;
+  }
+  // the first `rows` waves finish a row each
+  const bool out = wave < rows && colp < p.Np && s < g.kw && ch < g.c;
+  const int row = row0 + wave, tap = r * g.kw + s;
+  const int64_t ia = out ? (int64_t)tap * g.o + row : 0;
+  Sum SA;
+  if constexpr (PSQ)
+    SA = p.sumAd[ia];
+  else
+    SA = p.sumA[ia];
+  __shared__ Sum srow[GR_WAVES][64], scol[GR_WAVES][64];
+  Sum sum = add(vr, q, sl, S), SB = add(vc, wave, W, NC);
+  for (int e0 = q + GR_BATCH * sl; e0 < S; e0 += GR_BATCH * sl) {
+    load(vr, myrow, e0, sl, S);
+    sum += add(vr, e0, sl, S);
+  }
+  for (int e0 = wave + CB * W; e0 < NC; e0 += CB * W) {
+    load_col(vc, e0, W, NC);
+    SB += add(vc, e0, W, NC);
+  }
+  srow[wave][lane] = sum;
+  scol[wave][lane] = SB;
   __syncthreads();
-  if (wave != 0 || idx >= MN) return;
-  const Sum sum = (sw[0][lane] + sw[1][lane]) + (sw[2][lane] + sw[3][lane]);
+  if (!out) return;
+  sum = 0;
+  SB = 0;
+  for (int w = 0; w < sl; ++w) sum += srow[wave * sl + w][lane];
+  for (int w = 0; w < W; ++w) SB += scol[w][lane];
   int ylo, yhi, xlo, xhi;
   gradw_tap_range(r, g.stride, g.pad, g.h, g.ho, ylo, yhi);
   gradw_tap_range(s, g.stride, g.pad, g.w, g.wo, xlo, xhi);
@@ -549,21 +628,13 @@ __device__ __forceinline__ void gradw_reduce(const ConvGradwParams& p, const Con
   const double zB = (double)p.zeroB[0] + (double)p.halfB * dB;
   double v;
   if constexpr (PSQ) {
-    double wbs = 0.0;
-    for (int i = 0; i < 2 * p.splits; ++i) wbs += p.sumBd[(int64_t)i * p.Np + colp];
-    v = dB * (double)sum + zB * p.sumAd[(int64_t)tap * g.o + row] + dB * wbs + zB * cnt * p.zsum[0];
+    v = dB * sum + zB * SA + dB * SB + zB * cnt * p.zsum[0];
   } else {
     const double dA = 1.0 / (double)p.scaleA[0];
     const double zA = (double)p.zeroA[0] + (double)p.halfA * dA;
-    v = dA * dB * (double)sum + dA * zB * (double)p.sumA[(int64_t)tap * g.o + row] + zA * dB * (double)p.sumB[colp] +
-        cnt * (double)g.n * zA * zB;
+    v = dA * dB * (double)sum + dA * zB * (double)SA + zA * dB * (double)SB + cnt * (double)g.n * zA * zB;
   }
-  p.out[ic] = (float)v;
-}
-
-template <bool PSQ>
-__global__ __launch_bounds__(256) void conv_gradw_reduce_kernel(ConvGradwParams p, ConvGeom g) {
-  gradw_reduce<PSQ>(p, g, blockIdx.x);
+  p.out[((int64_t)row * g.kh * g.kw + tap) * g.c + ch] = (float)v;
 }
 
 // ---------------------------------------------------------------------------
@@ -637,13 +708,15 @@ hipError_t launch_conv_sums(const ConvGradwParams& p, const ConvGeom& g, bool ps
 }
 
 hipError_t launch_conv_gradw_reduce(const ConvGradwParams& p, const ConvGeom& g, bool psq, hipStream_t s) {
-  const int64_t MN = (int64_t)g.o * g.kh * g.kw * g.c;
-  if (MN < 1 || (MN + 63) / 64 > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((MN + 63) / 64));
+  const int lsl = gradw_log2_split_lanes(p.splits), sl = 1 << lsl;
+  const int waves = sl > 4 ? sl : 4;
+  const int64_t blocks = (int64_t)g.o * sl / waves * ((p.Np + 63) / 64);
+  if (blocks < 1 || blocks > 0x7FFFFFFF || (g.o & 15) != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), threads(64 * waves);
   if (psq)
-    hipLaunchKernelGGL(conv_gradw_reduce_kernel<true>, grid, dim3(256), 0, s, p, g);
+    hipLaunchKernelGGL(conv_gradw_reduce_kernel<true>, grid, threads, 0, s, p, g, lsl);
   else
-    hipLaunchKernelGGL(conv_gradw_reduce_kernel<false>, grid, dim3(256), 0, s, p, g);
+    hipLaunchKernelGGL(conv_gradw_reduce_kernel<false>, grid, threads, 0, s, p, g, lsl);
   return hipGetLastError();
 }
 

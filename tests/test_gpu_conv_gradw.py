@@ -66,6 +66,30 @@ def test_conv_grad_w_layouts(case, qb_w):
                 assert err(gX.cpu().numpy(), r["grad_X64"]) <= 1e-5
 
 
+@pytest.mark.parametrize("qb_w", ["ptq", "psq"])
+@pytest.mark.parametrize("case", [
+    # n, c, h, w, o, kh, kw, stride, pad
+    (9, 16, 11, 11, 16, 1, 1, 1, 0),   # per tensor 9 splits: two waves per row, two batches
+    (33, 3, 16, 16, 16, 3, 3, 1, 1),   # per tensor 72 splits
+    (260, 3, 9, 8, 32, 3, 3, 1, 1),    # per sample: many splits, several batches of column sums
+    (16, 64, 40, 40, 16, 3, 3, 2, 1),  # five column tiles
+    (40, 4, 40, 40, 48, 3, 3, 1, 1),   # per tensor over 400 splits
+], ids=lambda c: "x".join(map(str, c)))
+def test_conv_grad_w_split_counts(case, qb_w):
+    from paper_2010_14298_amd import fqt as f
+    n, c, h, w, o, kh, kw, st, pad = case
+    rng = np.random.default_rng(sum(case))
+    X = np.maximum(rng.standard_normal((n, h, w, c)), 0).astype(np.float32)
+    W = rng.standard_normal((o, kh, kw, c)).astype(np.float32)
+    ho, wo = (h + 2 * pad - kh) // st + 1, (w + 2 * pad - kw) // st + 1
+    G = synth.lognormal_row_gradient(rng, n, ho * wo * o).reshape(n, ho, wo, o)
+    r = BW.conv_backward(X, W, G, st, pad, qb_x=("psq", 8, 0), qb_w=(qb_w, 8, 0), seed=4)
+    gW, _, ws = f.fqt_conv_backward_im2col(dev(X, 0), dev(W, 0), dev(G, 0), st, pad, qb_x=("psq", 8, 0),
+                                           qb_w=(qb_w, 8, 0), seed=4, input_grad=False)
+    assert f.fqt_workspace_status(ws) == 0
+    assert err(gW.cpu().numpy(), r["grad_W64"]) <= 1e-5
+
+
 @pytest.mark.parametrize("c", [1, 16])
 def test_zero_point_sums_beyond_32_bits(c):
     # 257 * 256 * 256 pixels, nearly all of them at the lowest code (-128) on both sides: the code
