@@ -61,8 +61,8 @@ struct GradwCfg {
 };
 
 // A block walks the 128-pixel stages of its split (one range of pixels), or,
-// with a per-sample Q_b1, of each of its split's samples in turn; pixels past
-// the range (sample) load zeros.
+// with a per-sample Q_b1, a range of the samples' stages in order (whole samples
+// or part of one); pixels past the range (sample) load zeros.
 template <int BM, bool PSQ, bool LIN>
 __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(ConvGradwParams p, ConvGeom g) {
   using C = GradwCfg<BM>;
@@ -88,13 +88,13 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
   }
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * C::BN;
   const int howo = g.ho * g.wo;
-  // first pixel (sample) and number of stages
+  // first pixel (PSQ: stage) and number of stages
   const int spn = (howo + C::BK - 1) / C::BK;  // stages per sample (PSQ)
   int64_t first = (int64_t)split * p.per_split, last = first + p.per_split;
-  const int64_t total = PSQ ? (int64_t)g.n : (int64_t)g.n * howo;
+  const int64_t total = (int64_t)g.n * (PSQ ? spn : howo);
   if (first > total) first = total;
   if (last > total) last = total;
-  const int nk = PSQ ? (int)(last - first) * spn : (int)((last - first + C::BK - 1) / C::BK);
+  const int nk = PSQ ? (int)(last - first) : (int)((last - first + C::BK - 1) / C::BK);
 
   // ---- per-lane load state
   const int8_t* const zero16 = gradw_zero16;
@@ -127,7 +127,9 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
   const int8_t* bptr[C::B_INS];   // LIN
   int bleft[C::B_INS];            // LIN: pixels left in the tensor; PSQ: in the sample
   const uint32_t lin_end = (uint32_t)g.n * (uint32_t)(g.h * Wp);
-  int lsmp = 0, lst = 0;  // sample (from first) and stage in it of the next stage to load (PSQ)
+  // PSQ: sample and stage in it of the next stage to load, and of the next to add up
+  int lsmp = PSQ ? (int)(first / spn) : 0, lst = PSQ ? (int)(first - (int64_t)lsmp * spn) : 0;
+  int csmp = lsmp, cst = lst;
   // position the walk at pixel p0 of the whole tensor, `left` pixels before its end
   auto seek = [&](int64_t p0, int left) {
 #pragma unroll
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
     }
   };
   if constexpr (PSQ)
-    seek(first * howo, howo);
+    seek((int64_t)lsmp * howo + C::BK * lst, howo - C::BK * lst);
   else
     seek(first, (int)(last - first));
 
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
       if (++lst == spn) {
         lst = 0;
         ++lsmp;
-        seek((first + lsmp) * howo, howo);
+        seek((int64_t)lsmp * howo, howo);
       }
     }
   };
@@ -277,15 +279,13 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
     static_assert(C::PER <= 8, "one load slot per MFMA");
     if (more) loaded();
   };
-  // PSQ: after a sample's last stage its exact int32 sums join the float64
-  // ones, weighted by the sample's step 1 / s (column sums: by its zero point)
-  int csmp = 0, cst = 0;
-  auto flush = [&]() {
+  // PSQ: after a sample's last stage in the split its exact int32 sums join the
+  // float64 ones, weighted by the sample's step 1 / s (column sums: by its zero point)
+  auto flush = [&](int t) {
     if constexpr (PSQ) {
-      if (++cst < spn) return;
+      if (++cst < spn && t + 1 < nk) return;
       cst = 0;
-      const int64_t smp = first + csmp;
-      ++csmp;
+      const int64_t smp = csmp++;
       const double dA = 1.0 / (double)p.scaleA[smp];
       const double zA = (double)p.zeroA[smp] + (double)p.halfA * dA;
 #pragma unroll
@@ -318,14 +318,14 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
   // stage t reads buffer t % NS and fills buffer (t + NS - 1) % NS
   for (int t = 0; t < nk; t += C::NS) {
     stage(b0, C::NS == 2 ? b1 : b2, t);
-    flush();
+    flush(t);
     if (t + 1 < nk) {
       stage(b1, b0, t + 1);
-      flush();
+      flush(t + 1);
     }
     if (C::NS > 2 && t + 2 < nk) {
       stage(b2, b1, t + 2);
-      flush();
+      flush(t + 2);
     }
   }
   __syncthreads();
@@ -640,21 +640,34 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// Pixels (samples of a per-sample Q_b1) per split: at most 512 blocks, two per
+// Pixels (stages of a per-sample Q_b1) per split: at most 512 blocks, two per
 // CU, in a multiple of the XCD count of splits when there are that many; whole
-// 128-pixel stages, and at most 65536 pixels per int32 sum.
+// 128-pixel stages, and at most 65536 pixels per int32 sum.  A per-sample block
+// holds float64 sums too: one block per CU; whole samples where there are enough
+// of them, else ranges of their stages, a stage at least for every GRADW_PART
+// partial sums that the range writes (stages wait for their loads, about 1.5 us
+// each, but every range adds its partial sums to the reduction).  Layers, whole
+// samples / ranges: 3x3 3 -> 32 64x64 b128 139 / 110 us, 3x3 64 -> 64 56x56 b32
+// 144 / 119; 3x3 64 -> 128 28x28 b8 74.5 / 74.8 (80.6 without the least, 80.0
+// with 32768).
+constexpr int64_t GRADW_PART = 16384;
 void conv_gradw_splits(const ConvGeom& g, bool psq, int64_t& per_split, int& splits) {
   const int64_t bm = g.o <= 64 ? 64 : 128;
   const int64_t tiles = ((g.o + bm - 1) / bm) * ((conv_gradw_cols(g) + 127) / 128);
-  const int64_t unit = psq ? 1 : 128;
-  const int64_t units = psq ? g.n : ((int64_t)g.n * g.ho * g.wo + 127) / 128;
-  // a per-sample block holds float64 sums too: one block per CU
+  const int64_t howo = (int64_t)g.ho * g.wo, spn = (howo + 127) / 128;
   int64_t want = (psq ? 256 : 512) / tiles;
   if (want >= NUM_XCD) want = want / NUM_XCD * NUM_XCD;
+  const bool whole = g.n >= want;  // samples
+  const int64_t unit = psq ? (whole ? spn : 1) : 128;
+  const int64_t units = psq ? (whole ? g.n : g.n * spn) : (g.n * howo + 127) / 128;
   want = want > units ? units : want;
   want = want < 1 ? 1 : want;
   int64_t per = (units + want - 1) / want;
   if (!psq && per > 512) per = 512;
+  if (psq && !whole) {
+    const int64_t least = (g.o * conv_gradw_cols(g) + GRADW_PART - 1) / GRADW_PART;
+    per = per < least ? (least < spn ? least : spn) : per;
+  }
   int64_t n = (units + per - 1) / per;
   if (n >= NUM_XCD && n % NUM_XCD != 0) n = (n + NUM_XCD - 1) / NUM_XCD * NUM_XCD;  // trailing splits may be empty
   per_split = per * unit;

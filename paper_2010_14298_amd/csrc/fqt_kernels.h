@@ -384,7 +384,7 @@ struct ConvGradwParams {
   const int8_t* q1;
   const int8_t* xq;
   int64_t Np;         // partial-sum columns (conv_gradw_cols)
-  int64_t per_split;  // pixels per split (per-sample Q_b1: samples)
+  int64_t per_split;  // pixels per split (per-sample Q_b1: 128-pixel stages, each sample's rounded up)
   int splits;
   int32_t* part;      // [splits][o][Np]
   int64_t* sumB;      // [GRADW_SUMB][Np] parts of the X code sums over each column's valid pixels (cleared before)
