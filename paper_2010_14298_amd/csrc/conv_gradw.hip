@@ -644,33 +644,42 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
 // CU, in a multiple of the XCD count of splits when there are that many; whole
 // 128-pixel stages, and at most 65536 pixels per int32 sum.  A per-sample block
 // holds float64 sums too: one block per CU; whole samples where there are enough
-// of them, else ranges of their stages, a stage at least for every GRADW_PART
-// partial sums that the range writes (stages wait for their loads, about 1.5 us
-// each, but every range adds its partial sums to the reduction).  Layers, whole
-// samples / ranges: 3x3 3 -> 32 64x64 b128 139 / 110 us, 3x3 64 -> 64 56x56 b32
-// 144 / 119; 3x3 64 -> 128 28x28 b8 74.5 / 74.8 (80.6 without the least, 80.0
-// with 32768).
-constexpr int64_t GRADW_PART = 16384;
+// of them, else ranges of their stages (gradw_range).
+//
+// A range saves a block stages, which wait for their loads one after the other,
+// and adds its partial sums to the reduction: taken from two stages less on,
+// where it adds at most GRADW_PART partial sums per stage less.  Layers, whole
+// samples / ranges: 3x3 3 -> 32 64x64 b128 139 / 110 us, b4 83 / 42, 1x1 64 -> 64
+// 28x28 b4 57 / 49, 3x3 64 -> 64 56x56 b4 113 / 82; beyond the line 3x3 64 -> 128
+// 28x28 b32 98.5 / 103.5, 1x1 256 -> 128 28x28 b32 88.8 / 93.7.
+constexpr int64_t GRADW_PART = 65536;
+static int64_t gradw_range(int64_t n, int64_t spn, int64_t want, int64_t part) {
+  for (int64_t per = (n * spn + want - 1) / want; per + 2 <= spn; ++per)
+    if (((n * spn + per - 1) / per - n) * part <= (spn - per) * GRADW_PART) return per;
+  return spn;
+}
 void conv_gradw_splits(const ConvGeom& g, bool psq, int64_t& per_split, int& splits) {
   const int64_t bm = g.o <= 64 ? 64 : 128;
   const int64_t tiles = ((g.o + bm - 1) / bm) * ((conv_gradw_cols(g) + 127) / 128);
   const int64_t howo = (int64_t)g.ho * g.wo, spn = (howo + 127) / 128;
   int64_t want = (psq ? 256 : 512) / tiles;
   if (want >= NUM_XCD) want = want / NUM_XCD * NUM_XCD;
-  const bool whole = g.n >= want;  // samples
-  const int64_t unit = psq ? (whole ? spn : 1) : 128;
-  const int64_t units = psq ? (whole ? g.n : g.n * spn) : (g.n * howo + 127) / 128;
-  want = want > units ? units : want;
-  want = want < 1 ? 1 : want;
-  int64_t per = (units + want - 1) / want;
-  if (!psq && per > 512) per = 512;
-  if (psq && !whole) {
-    const int64_t least = (g.o * conv_gradw_cols(g) + GRADW_PART - 1) / GRADW_PART;
-    per = per < least ? (least < spn ? least : spn) : per;
+  if (want < 1) want = 1;
+  // in 128-pixel stages
+  const int64_t stages = psq ? g.n * spn : (g.n * howo + 127) / 128;
+  int64_t per;
+  if (!psq) {
+    if (want > stages) want = stages;
+    per = (stages + want - 1) / want;
+    if (per > 512) per = 512;
+  } else if (g.n >= want) {
+    per = (g.n + want - 1) / want * spn;
+  } else {
+    per = gradw_range(g.n, spn, want, g.o * conv_gradw_cols(g));
   }
-  int64_t n = (units + per - 1) / per;
+  int64_t n = (stages + per - 1) / per;
   if (n >= NUM_XCD && n % NUM_XCD != 0) n = (n + NUM_XCD - 1) / NUM_XCD * NUM_XCD;  // trailing splits may be empty
-  per_split = per * unit;
+  per_split = psq ? per : per * 128;
   splits = (int)n;
 }
 
