@@ -474,7 +474,11 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
   w.q2 = c.take<int8_t>(N * howo * g.o);
   // right after q2: grad_X reaches the 16 zero bytes from it by a 32-bit offset
   // in 16-byte steps, which the general plan's rows in between could exceed
-  const int64_t nsumB = GRADW_SUMB * conv_gradw_cols(g);
+  ConvGradwParams& p = w.gw;
+  p.Np = conv_gradw_cols(g);
+  conv_gradw_splits(g, psq1, p.per_split, p.splits);
+  p.copies = gradw_copies(p.splits);
+  const int64_t nsumB = p.copies * p.Np;
   w.ncounters = psq1 ? 4 : 4 + 2 * nsumB + howo * g.o;
   w.counters = c.take<int32_t>(w.ncounters);
   w.q1 = c.take<int8_t>(N * howo * g.o);
@@ -494,11 +498,8 @@ ConvWs carve_conv(Carver& c, const float* X, const float* W, const float* G, con
     if (w.bhq.general) w.tbuf = c.take<double>(hw * g.npad * g.c);
   }
   // grad_W
-  ConvGradwParams& p = w.gw;
   p.q1 = w.q1;
   p.xq = w.xq;
-  p.Np = conv_gradw_cols(g);
-  conv_gradw_splits(g, psq1, p.per_split, p.splits);
   const int64_t parts = (int64_t)p.splits * (psq1 ? g.o + 2 : g.o) * p.Np;
   if (psq1) {
     p.partd = c.take<double>(parts);

@@ -346,7 +346,7 @@ __global__ __launch_bounds__(GradwCfg<BM>::THREADS, 2) void conv_gradw_kernel(Co
       } else {
         const int c = csum[f] + __shfl_xor(csum[f], 32);
         if (lane < 32 && col < p.Np && c != 0)
-          atomicAdd(reinterpret_cast<unsigned long long*>(p.sumB) + (split % GRADW_SUMB) * p.Np + col,
+          atomicAdd(reinterpret_cast<unsigned long long*>(p.sumB) + (split & (p.copies - 1)) * p.Np + col,
                     (unsigned long long)(int64_t)c);
       }
     }
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) void conv_wsum_kernel(ConvGeom g, const int8_t
 //   per tensor: dA dB acc + dA zB SA[tap][o] + zA dB SB[col] + cnt zA zB
 //   per sample: dB sum_n dA_n acc_n + zB sum_n dA_n SA_n + dB sum_n zA_n SB_n
 //               + zB (valid pixels per sample) sum_n zA_n
-// A block takes 64 columns and W / sl rows of the partial sums: sl waves per
+// A block takes 64 output columns and W / sl rows: sl waves per
 // row, each over every sl-th split, and all W waves over the parts of the column
 // sums, a batch of loads of each in flight.  The waves' sums meet in LDS and are
 // added in a fixed order.  Loads waiting on each other are all there is to it,
@@ -538,10 +538,14 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
   using Sum = typename std::conditional<PSQ, double, int64_t>::type;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6, rows = W >> lsl, sl = 1 << lsl;
-  const int cols = (int)((p.Np + 63) / 64);
+  const int taps = g.kh * g.kw, N = taps * g.c, cols = (N + 63) / 64;
   const int row0 = (int)(blockIdx.x / cols) * rows;  // o is a multiple of 16: whole runs of rows
-  const int colp = (int)(blockIdx.x % cols) * 64 + lane;
-  const int64_t cc = colp < p.Np ? colp : p.Np - 1, pitch = (int64_t)(PSQ ? g.o + 2 : g.o) * p.Np;
+  // output column (tap, channel) and its column cc of the partial sums
+  const int col = (int)(blockIdx.x % cols) * 64 + lane;
+  const int tap = min(col, N - 1) / g.c, ch = min(col, N - 1) - tap * g.c;
+  const int r = tap / g.kw, s = tap - r * g.kw;
+  const int64_t cc = g.cp == 4 ? 16 * (r * ((g.kw + 3) / 4) + (s >> 2)) + 4 * (s & 3) + ch : tap * g.cp + ch;
+  const int64_t pitch = (int64_t)(PSQ ? g.o + 2 : g.o) * p.Np;
   typedef typename std::conditional<PSQ, double, int>::type Part;
   typedef typename std::conditional<PSQ, double, int64_t>::type Col;
   // one batch: entries e0, e0 + step, ... below n (past it: the first, dropped
@@ -557,7 +561,7 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
         v[u] = p.part[i];
     }
   };
-  constexpr int CB = PSQ ? GR_BATCH : GRADW_SUMB / 4;  // one batch of the copies for four waves
+  constexpr int CB = PSQ ? GR_BATCH : 4;  // at most 16 copies, at least four waves: one batch
   auto load_col = [&](Col (&v)[CB], int e0, int step, int n) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
@@ -575,27 +579,14 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
     return sum;
   };
   const int myrow = row0 + (wave >> lsl), q = wave & (sl - 1), S = p.splits;
-  const int NC = PSQ ? 2 * S : GRADW_SUMB;  // parts of the column sums
+  const int NC = PSQ ? 2 * S : p.copies;  // parts of the column sums
   Part vr[GR_BATCH];
   Col vc[CB];
   load(vr, myrow, q, sl, S);
   load_col(vc, wave, W, NC);
-  // partial column -> tap and channel (none: padding)
-  int r, s, ch;
-  if (g.cp == 4) {
-    const int q4 = (g.kw + 3) / 4, chunk = colp / 16;
-    r = chunk / q4;
-    s = 4 * (chunk - r * q4) + ((colp & 15) >> 2);
-    ch = colp & 3;
-  } else {
-    const int tap = colp / g.cp;
-    ch = colp - tap * g.cp;
-    r = tap / g.kw;
-    s = tap - r * g.kw;
-  }
   // the first `rows` waves finish a row each
-  const bool out = wave < rows && colp < p.Np && s < g.kw && ch < g.c;
-  const int row = row0 + wave, tap = r * g.kw + s;
+  const bool out = wave < rows && col < N;
+  const int row = row0 + wave;
   const int64_t ia = out ? (int64_t)tap * g.o + row : 0;
   Sum SA;
   if constexpr (PSQ)
@@ -634,7 +625,7 @@ __global__ __launch_bounds__(64 * GR_WAVES) void conv_gradw_reduce_kernel(ConvGr
     const double zA = (double)p.zeroA[0] + (double)p.halfA * dA;
     v = dA * dB * (double)sum + dA * zB * (double)SA + zA * dB * (double)SB + cnt * (double)g.n * zA * zB;
   }
-  p.out[((int64_t)row * g.kh * g.kw + tap) * g.c + ch] = (float)v;
+  p.out[(int64_t)row * N + col] = (float)v;
 }
 
 // ---------------------------------------------------------------------------
@@ -732,7 +723,7 @@ hipError_t launch_conv_sums(const ConvGradwParams& p, const ConvGeom& g, bool ps
 hipError_t launch_conv_gradw_reduce(const ConvGradwParams& p, const ConvGeom& g, bool psq, hipStream_t s) {
   const int lsl = gradw_log2_split_lanes(p.splits), sl = 1 << lsl;
   const int waves = sl > 4 ? sl : 4;
-  const int64_t blocks = (int64_t)g.o * sl / waves * ((p.Np + 63) / 64);
+  const int64_t blocks = (int64_t)g.o * sl / waves * (((int64_t)g.kh * g.kw * g.c + 63) / 64);
   if (blocks < 1 || blocks > 0x7FFFFFFF || (g.o & 15) != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), threads(64 * waves);
   if (psq)

@@ -376,10 +376,16 @@ struct ConvGeom {
 // grad_W (conv_gradw.hip): Q_b1 codes [pixel][o] and X codes in pixel order,
 // both in sample order; partial sums over splits of the output pixels, then the
 // reduction with the zero-point terms.
-// Copies of the X code sums, split s adding to copy s % GRADW_SUMB: with one,
-// the atomics of many splits of few columns queue up for longer than the
-// contraction takes (3x3 3 -> 32 64x64 b128, 512 splits: 22 of 36 us).
-constexpr int GRADW_SUMB = 16;
+// Copies of the X code sums (a power of two, at most 16), split s adding to copy
+// s % copies: one for every 16 splits.  With one copy the atomics of many splits
+// of few columns queue up for longer than the contraction takes (3x3 3 -> 32
+// 64x64 b128, 512 splits: 22 of 36 us); every block of the reduction reads all of
+// them, a few bytes beside the partial sums of as many splits.
+inline int gradw_copies(int splits) {
+  int c = 1;
+  while (c < 16 && splits > 16 * c) c *= 2;
+  return c;
+}
 struct ConvGradwParams {
   const int8_t* q1;
   const int8_t* xq;
@@ -387,7 +393,8 @@ struct ConvGradwParams {
   int64_t per_split;  // pixels per split (per-sample Q_b1: 128-pixel stages, each sample's rounded up)
   int splits;
   int32_t* part;      // [splits][o][Np]
-  int64_t* sumB;      // [GRADW_SUMB][Np] parts of the X code sums over each column's valid pixels (cleared before)
+  int copies;         // of sumB
+  int64_t* sumB;      // [copies][Np] parts of the X code sums over each column's valid pixels (cleared before)
   int32_t* qs;        // [ho wo][o] Q_b1 code sums over the samples (cleared before)
   int64_t* sumA;      // [tap][o] ... over the tap's valid pixels
   // per-sample Q_b1: the same in float64, weighted by 1 / s_n (the X code sums by z_n + half / s_n)

@@ -1264,13 +1264,17 @@ static bool pitch_ok(const QuantParams& p) {
 }
 
 // The quantizer is the last reader of its float32 inputs in a step (the
-// statistics read them before).  Inputs that leave no room for themselves and
-// the codes in the 256 MB last-level cache are read nontemporally, so that the
-// codes stay in it for the contractions; smaller ones stay cached for whoever
-// reads them next.  With / without: FFN layer (184 MB of inputs) 200.3 / 208.3
-// us, 8192 x 4096 block Householder quantizer (134 MB) 75.0 / 79.2, 3x3 64ch
-// 56x56 b128 (206 MB) 240.6 / 246.9; 3x3 s2 128ch 56x56 b256 (514 MB) 475 / 478,
-// with the conv launch's order from the end 462 (the order alone: 475); 3001 x 1024 -> 4096 (78 MB) 121.0 / 117.7.
+// statistics read them before): large ones are read nontemporally, so that the
+// codes stay in the 256 MB last-level cache for the contractions.  Where that
+// pays depends on what the cache holds when the pass begins (ordinary /
+// nontemporal, us).  New inputs in every pass gain from about 75 MB on: layers
+// of 56 MB of inputs 96.0 / 96.7, 86 MB 122.5 / 120.9, 116 MB 165.6 / 162.0, 176
+// MB (8192 x 1024 -> 4096) 205.6 / 195.1, 3x3 conv of 196 MB 243.5 / 237.7, block
+// Householder quantizer of 64 MB 47.6 / 48.0, 128 MB 76.2 / 75.0, 160 MB 98.4 /
+// 93.5.  The same inputs in every pass stay in the cache from one to the next, and
+// gain from about 165 MB on: 86 MB 119.8 / 121.2, 136 MB 173.2 / 176.2, 176 MB
+// 197.4 / 193.7, quantizer of 128 MB 72.3 / 75.2.  The line lies between the two,
+// nearer to the first, which is how a training step meets its inputs.
 static int quant_nt(int64_t floats) { return floats * 4 >= (int64_t)100 << 20; }
 
 // Rows of whole float4s: one 16-byte load and one Philox block per lane and
@@ -1515,7 +1519,8 @@ __device__ __forceinline__ void quant_conv_w(const ConvWQParams& p, int64_t bloc
 // Blocks [0, nbw) the weights; of the rest every period-th (while they last) a
 // run of X words, the others the gradient tiles, both from the end: the
 // statistics read the inputs from the beginning, so the end is what the
-// last-level cache still holds of larger ones.
+// last-level cache still holds of larger ones (3x3 s2 128ch 56x56 b256, 514 MB
+// of inputs: 475 us from the beginning, 462 from the end).
 template <int MODE, int K, int H2, bool VEC>
 __global__ __launch_bounds__(256) void quant_conv_kernel(QuantParams pg, PixelQParams px, ConvWQParams pw, int64_t nbw,
                                                          int64_t nbx, int64_t period, int64_t ctg) {
