@@ -659,7 +659,7 @@ static hipError_t launch_conv_gradx_nt(const GemmParams& p, const ConvGeom& g, c
 template <int EPI, int KE>
 static hipError_t launch_conv_gradx_t(const GemmParams& p, const ConvGeom& g, const int8_t* q2, const int8_t* zero16,
                                       const int32_t* sg, const int32_t* swq, hipStream_t s) {
-  return stream_rows(p.out, p.ldo, STREAM_CONV) ? launch_conv_gradx_nt<EPI, KE, true>(p, g, q2, zero16, sg, swq, s)
+  return stream_rows(p.out, p.M, p.ldo, STREAM_CONV) ? launch_conv_gradx_nt<EPI, KE, true>(p, g, q2, zero16, sg, swq, s)
                                       : launch_conv_gradx_nt<EPI, KE, false>(p, g, q2, zero16, sg, swq, s);
 }
 

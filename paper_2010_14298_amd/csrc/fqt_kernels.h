@@ -308,8 +308,11 @@ hipError_t launch_splitk_reduce(const GemmParams& p, int64_t* out64, int epi, hi
 // line meet in L2 with those that fill it; nontemporal ones go out as they are,
 // and a part of a line costs memory a read as well.  The unit lies where that
 // outweighs the gain, nontemporal / ordinary in us:
-// - STREAM_TENSOR, one float per lane (runs of 128 bytes): whole lines.  Forward
-//   8192 x 512 -> 4096 75 / 77, -> 4080 (64-byte rows) 97 / 79, -> 4095 95 / 78.
+// - STREAM_TENSOR, one float per lane (runs of 128 bytes): whole lines (forward
+//   8192 x 512 -> 4096 75 / 77, -> 4095 95 / 78), and half lines up to 96 MB of
+//   output, which the last-level cache still puts together (forwards of 6832 rows
+//   by 512: 784 wide 34.0 / 35.4, 1360 44.4 / 46.0, 2544 60.8 / 61.9, 3568 (97
+//   MB) 64.9 / 64.8, 4080 77.1 / 73.7; 8192 rows 4080 97 / 79).
 // - STREAM_ROW, four floats per lane (runs of 256 bytes): half lines.  Layer
 //   8192 x 1008 -> 512 97.7 / 98.4, 8192 x 1020 -> 512 104 / 99, 8192 x 4095 ->
 //   128 343 / 186.
@@ -318,8 +321,9 @@ hipError_t launch_splitk_reduce(const GemmParams& p, int64_t* out64, int epi, hi
 //   104ch 310 / 324; only wide odd pitches lose (1x1 196ch 469 / 439).  Without
 //   whole 16 bytes the stores are single floats: 3x3 83ch 470 / 320.
 enum StreamUnit { STREAM_TENSOR = 32, STREAM_ROW = 16, STREAM_CONV = 4 };
-inline bool stream_rows(const float* out, int64_t ldo, StreamUnit unit) {
-  return ldo % unit == 0 && (uintptr_t)out % (4 * unit) == 0;
+inline bool stream_rows(const float* out, int64_t rows, int64_t ldo, StreamUnit unit) {
+  const int64_t u = unit == STREAM_TENSOR && rows * ldo * 4 <= (int64_t)96 << 20 ? STREAM_ROW : unit;
+  return ldo % u == 0 && (uintptr_t)out % (4 * u) == 0;
 }
 
 // Zero-point term of a contraction over samples whose A rows (samples) carry

@@ -489,7 +489,7 @@ static hipError_t launch_gemm_nt(const GemmParams& p, hipStream_t s) {
 template <class C, int EPI, int KG>
 static hipError_t launch_gemm_t(const GemmParams& p, hipStream_t s) {
   if constexpr (EPI != EPI_RAW_I32) {
-    if (stream_rows(p.out, p.ldo, EPI == EPI_TENSOR ? STREAM_TENSOR : STREAM_ROW)) return launch_gemm_nt<C, EPI, KG, true>(p, s);
+    if (stream_rows(p.out, p.M, p.ldo, EPI == EPI_TENSOR ? STREAM_TENSOR : STREAM_ROW)) return launch_gemm_nt<C, EPI, KG, true>(p, s);
   }
   return launch_gemm_nt<C, EPI, KG, false>(p, s);
 }
