@@ -108,9 +108,10 @@ __global__ __launch_bounds__(256) void stats_kernel(StatsPlan sp) {
   int si = 0;
   while (si + 1 < sp.nseg && (int64_t)blockIdx.x >= sp.block_start[si + 1]) ++si;
   const StatsSeg g = sp.seg[si];
-  const int64_t b = (int64_t)blockIdx.x - sp.block_start[si];
-  const int64_t row = b / g.chunks;
-  const int64_t c_begin = (b % g.chunks) * g.chunk;
+  // at most 2^31 - 1 blocks: a 32-bit division
+  const uint32_t b = blockIdx.x - (uint32_t)sp.block_start[si], chunks = (uint32_t)g.chunks;
+  const int64_t row = b / chunks;
+  const int64_t c_begin = (b - (uint32_t)row * chunks) * g.chunk;
   const int64_t c_end = (c_begin + g.chunk < g.cols) ? c_begin + g.chunk : g.cols;
   const float* xr = g.x + row * g.cols;
   float mn = INFINITY, mx = -INFINITY;
@@ -1223,22 +1224,23 @@ __global__ __launch_bounds__(256) void quant_tile_kernel(QuantParams p) {
 // each matrix's own affair (VECG, vecx, vecw): an odd width of X and W leaves
 // the gradient its float4 tiles.
 template <int MODE, int K, int H2, bool VECG>
-__global__ __launch_bounds__(256) void quant_fused_kernel(QuantParams pg, QuantParams px, QuantParams pw, int64_t nbx,
-                                                          int64_t nbw, int64_t period, int64_t ctg, int64_t ctx,
-                                                          int64_t ctw, bool vecx, bool vecw) {
-  const int64_t b = blockIdx.x;
-  const int64_t nxw = nbx + nbw;
-  if (b % period == period - 1 && b / period < nxw) {
-    const bool x = b / period < nbx;
-    const int64_t t = b / period - (x ? 0 : nbx), ct = x ? ctx : ctw;
+__global__ __launch_bounds__(256) void quant_fused_kernel(QuantParams pg, QuantParams px, QuantParams pw, uint32_t nbx,
+                                                          uint32_t nbw, uint32_t period, uint32_t ctg, uint32_t ctx,
+                                                          uint32_t ctw, bool vecx, bool vecw) {
+  // at most 2^31 - 1 blocks (checked at launch): 32-bit divisions, which every
+  // block waits for (128 x 256 -> 256 layer 37.0 us with 64-bit ones, 36.8)
+  const uint32_t b = blockIdx.x, nxw = nbx + nbw, run = b / period;
+  if (b - run * period == period - 1 && run < nxw) {
+    const bool x = run < nbx;
+    const uint32_t t = run - (x ? 0 : nbx), ct = x ? ctx : ctw;
     const QuantParams& p = x ? px : pw;
     if (x ? vecx : vecw)
       quant_tile<QM_TENSOR, 0, 0, true, true>(p, t % ct, t / ct);
     else
       quant_tile<QM_TENSOR, 0, 0, false, true>(p, t % ct, t / ct);
   } else {
-    const int64_t before = (b + 1) / period < nxw ? (b + 1) / period : nxw;
-    const int64_t t = b - before;
+    // not the last of its run: as many X / W tiles before it as whole runs
+    const uint32_t t = b - (run < nxw ? run : nxw);
     quant_tile<MODE, K, H2, VECG, false>(pg, t % ctg, t / ctg);
   }
 }
@@ -1295,8 +1297,9 @@ static hipError_t launch_quant_fused_v(QuantParams pg, QuantParams px, QuantPara
   const int64_t nb = nbg + nbx + nbw;
   if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
   const int64_t period = nb / (nbx + nbw);
-  hipLaunchKernelGGL((quant_fused_kernel<MODE, K, H2, VECG>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw, nbx, nbw,
-                     period, ctg, ctx, ctw, quant_vec(px), quant_vec(pw));
+  hipLaunchKernelGGL((quant_fused_kernel<MODE, K, H2, VECG>), dim3((unsigned)nb), dim3(256), 0, s, pg, px, pw,
+                     (uint32_t)nbx, (uint32_t)nbw, (uint32_t)period, (uint32_t)ctg, (uint32_t)ctx, (uint32_t)ctw,
+                     quant_vec(px), quant_vec(pw));
   return hipGetLastError();
 }
 
