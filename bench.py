@@ -48,11 +48,11 @@ def parse():
 TRAFFIC_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "traffic_linear_ffn_bhq5.txt")
 COUNTER_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "counters_linear_ffn_bhq5.json")
 SEEDS_COUNTER_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "counters_seed_batch.json")
-# kernel of each phase in the rocprofv3 summaries (name prefixes)
+# kernel of each phase in the rocprofv3 summaries (parts of its name)
 PHASE_KERNEL = {
-    "quant_G": ("quant_fused_kernel<2, 64, 1>",),
-    "gemm_gradX": ("gemm_i8_kernel<fqt::TileCfg<256", ", 3, 64, true>"),
-    "gemm_gradW": ("gemm_i8_kernel<fqt::TileCfg<128", ", 1, 0, true>"),
+    "quant_G": ("quant_fused_kernel<2, 64, 1, true>",),
+    "gemm_gradX": ("gemm_i8_kernel<fqt::TileCfg<256", ", 3, 64, true, false"),
+    "gemm_gradW": ("gemm_i8_kernel<fqt::TileCfg<128", ", 1, 0, true, false"),
 }
 
 

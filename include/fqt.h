@@ -196,9 +196,11 @@ typedef struct {
 /* Optional per-phase timing: when fqt_bwd_cfg.trace is non-NULL, the layer
  * backward records start[i] / stop[i] (caller-created hipEvent_t handles)
  * around phase i on `stream`, for i < count.  Phases of the layer backward:
- *   0 workspace init   1 stats X, W, G   2 scales / BHQ plan
- *   3 quantize X       4 quantize W      5 quantize G (Q_b1 and Q_b2)
- *   6 grad_W contraction (with any split-K reduction)
+ *   0 empty            1 stats X, W, G   2 scales / BHQ plan
+ *   3, 4 empty         5 all four quantizations, one launch (linear with an
+ *                        FQT_SHIFT Q_b1: and its zero-point column terms)
+ *   6 grad_W contraction (with any split reduction; conv: and the zero-point
+ *     sums of both contractions, the row sums that grad_X uses among them)
  *   7 grad_X contraction                                                    */
 #define FQT_TRACE_PHASES 8
 typedef struct {

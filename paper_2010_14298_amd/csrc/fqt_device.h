@@ -67,32 +67,14 @@ __device__ __forceinline__ u32x4 philox_of_block(uint64_t blk, uint64_t seed, ui
   k1 += PHILOX_W1;
   return philox_rounds(n0, c1, n2, c3, k0, k1, PHILOX_ROUNDS - 2);
 }
-__device__ __forceinline__ u32x4 philox_block(uint64_t e, uint64_t seed, uint32_t stream) {
-  return philox_of_block(e >> 2, seed, stream);
-}
-
-__device__ __forceinline__ uint32_t philox_word(const u32x4& o, int i) {
-  return i == 0 ? o.x : (i == 1 ? o.y : (i == 2 ? o.z : o.w));
-}
 
 // ---------------------------------------------------------------------------
 // Stochastic rounding with a 24-bit uniform (Sec. 3.3), the low 24 bits of
 // the Philox word:
 //   fl = floor(y); frac = y - fl; round up iff float(word & 0xFFFFFF) < frac * 2^24;
-//   code clamped to [0, B].
-// fl is clamped to [-1, B] first, which leaves the clamped code unchanged and
-// keeps the integer conversion in range.
+//   code clamped to [0, B]
+// (sr_top below, in fixed point).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int sr_code(float y, uint32_t word, int B) {
-  float fl = floorf(y);
-  const float frac = y - fl;
-  const float thr = frac * 16777216.0f;
-  const float u = (float)(word & 0xFFFFFFu);
-  fl = fminf(fmaxf(fl, -1.0f), (float)B);
-  int c = (int)fl + (u < thr ? 1 : 0);
-  return min(max(c, 0), B);
-}
-
 // Deterministic round-half-to-even, clamped to [0, B] (Q_f, Q_theta).
 __device__ __forceinline__ int rne_code(float y, int B) {
   float r = rintf(y);
@@ -107,11 +89,11 @@ __device__ __forceinline__ int rne_code(float y, int B) {
 // permutes and sum with one 4-way int8 dot product.
 //
 // sr_top: with yc = clamp(y, 0, B) (clamping first leaves the clamped code
-// of sr_code unchanged), T = ceil(yc * 2^24) = floor(yc) * 2^24 + ceil(frac
+// unchanged), T = ceil(yc * 2^24) = floor(yc) * 2^24 + ceil(frac
 // * 2^24) (the scaling is exact and floor(yc) * 2^24 is an integer), u =
 // word & 0xFFFFFF and u' = 2^24 - 1 - u = ~word & 0xFFFFFF, the sum T + u'
 // carries into bit 24 exactly when u < ceil(frac * 2^24), i.e. when u <
-// frac * 2^24: the rounding-up decision of sr_code.  T + u' < 2^32 since
+// frac * 2^24: the rounding-up decision.  T + u' < 2^32 since
 // yc <= 255 and at yc = B the fraction is 0.  -hoff only has top-byte bits
 // and u' only low ones, so u' - hoff is one three-input logic operation.
 // ---------------------------------------------------------------------------

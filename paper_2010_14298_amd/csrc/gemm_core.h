@@ -1,7 +1,7 @@
 // Shared int8 matrix-core contraction core (gfx950): tile shapes, 16-byte
-// operand chunks, and the double-buffered K loop on v_mfma_i32_32x32x32_i8.
-// Used by the linear-layer contractions (gemm.hip) and the conv ones
-// (conv.hip).
+// operand chunks, and the K loops on v_mfma_i32_32x32x32_i8.  Used by the
+// linear-layer contractions (gemm.hip); the conv kernels share its types and
+// block order.
 #pragma once
 
 #include "fqt_device.h"
@@ -36,8 +36,7 @@ struct TileCfg {
 // Configurations measured best on MI355X for the layer shapes (8 waves each).
 using CfgLarge = TileCfg<256, 128, 64, 64, 128, 3>;
 using CfgSmall = TileCfg<128, 128, 32, 64, 128, 4>;
-// at most 64 rows (the conv grad_W contraction over output channels): no
-// half-empty 128-row tiles
+// raw int32 products of at most 64 rows: no half-empty 128-row tiles
 using CfgNarrow = TileCfg<64, 128, 32, 64, 128, 3>;
 
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
@@ -101,24 +100,13 @@ __device__ __forceinline__ void tile_mn(int64_t tile, int64_t tiles_m, int64_t t
 // rows and a K range that is a whole number of 128-byte stages.  The generic
 // one (register-staged, two LDS buffers) takes both operands through loaders
 // (16-byte chunks, zero outside the operand and past the end of K, where the
-// loop also loads), which is how the conv input-gradient contraction gathers
-// its implicit im2col rows, and handles ragged K and unaligned rows.  An A
-// loader maps a row once to a per-row state (`row`), then loads 16-byte
-// chunks of it (`load`) stage by stage, so per-row index arithmetic stays out
-// of the K loop; a thread's chunks of one stage share their K offset, decoded
-// once (`kstate`).
+// loop also loads), and handles ragged K, unaligned rows and packed codes.
 struct PlainALoader {
   const int8_t* A;
   int64_t lda, M, kend;
   bool aligned;
-  struct Row {
-    int64_t r;
-  };
-  typedef int64_t KState;
-  __device__ __forceinline__ Row row(int64_t r) const { return Row{r}; }
-  __device__ __forceinline__ KState kstate(int64_t k) const { return k; }
-  __device__ __forceinline__ Chunk16 load(const Row& rw, const KState& k) const {
-    return load_chunk(A, lda, rw.r, M, k, kend, aligned);
+  __device__ __forceinline__ Chunk16 load(int64_t r, int64_t k) const {
+    return load_chunk(A, lda, r, M, k, kend, aligned);
   }
 };
 
@@ -129,12 +117,6 @@ struct PlainALoader {
 struct PackedALoader {
   const int8_t* A;
   int64_t lda, M, kend;  // lda in bytes
-  struct Row {
-    int64_t r;
-  };
-  typedef int64_t KState;
-  __device__ __forceinline__ Row row(int64_t r) const { return Row{r}; }
-  __device__ __forceinline__ KState kstate(int64_t k) const { return k; }
   // 8 nibbles of w -> 8 offset codes in two words
   __device__ __forceinline__ static void unpack8(uint32_t w, uint32_t& o0, uint32_t& o1) {
     const uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
@@ -142,10 +124,10 @@ struct PackedALoader {
     o0 = (__builtin_amdgcn_perm(hi, lo, 0x05010400u) + 0x78787878u) ^ 0x80808080u;
     o1 = (__builtin_amdgcn_perm(hi, lo, 0x07030602u) + 0x78787878u) ^ 0x80808080u;
   }
-  __device__ __forceinline__ Chunk16 load(const Row& rw, const KState& k) const {
+  __device__ __forceinline__ Chunk16 load(int64_t r, int64_t k) const {
     Chunk16 c{{0u, 0u, 0u, 0u}};
-    if (rw.r >= M || k >= kend) return c;
-    const uint2 v = *reinterpret_cast<const uint2*>(A + rw.r * lda + (k >> 1));
+    if (r >= M || k >= kend) return c;
+    const uint2 v = *reinterpret_cast<const uint2*>(A + r * lda + (k >> 1));
     unpack8(v.x, c.w[0], c.w[1]);
     unpack8(v.y, c.w[2], c.w[3]);
     return c;
@@ -291,27 +273,18 @@ __device__ __forceinline__ void dma_mainloop(const GemmParams& p, int8_t* __rest
   __syncthreads();
 }
 
-// K offsets of the stages a K loop runs: stage t starts at kbeg + t bk, n
-// stages (offsets past the end load zero chunks)
-struct KRange {
-  int64_t kbeg, bk, n;
-  __device__ __forceinline__ int64_t k(int64_t t) const { return kbeg + t * bk; }
-};
-
-// The register-staged K loop over the stages of a stage map KM (km.n stages,
-// stage t at K offset km.k(t); for t >= km.n, km.k(t) must lie past the
-// loaders' K range so that they load zeros).
-template <class C, class ALoader, class BLoader, class KM>
-__device__ __forceinline__ void generic_mainloop_km(const GemmParams& p, const ALoader& aload, const BLoader& bload,
-                                                    int8_t* lds, int64_t m0, int64_t n0, const KM& km,
-                                                    v16i (&acc)[C::IT][C::JT]) {
+// The register-staged K loop over [kbeg, kend); stages past the end load zeros.
+template <class C, class ALoader, class BLoader>
+__device__ __forceinline__ void generic_mainloop(const GemmParams& p, const ALoader& aload, const BLoader& bload,
+                                                 int8_t* lds, int64_t m0, int64_t n0, int64_t kbeg, int64_t kend,
+                                                 v16i (&acc)[C::IT][C::JT]) {
   int8_t* sA = lds;                          // [2][BM * C::LDS_STRIDE]
   int8_t* sB = lds + 2 * C::BM * C::LDS_STRIDE;  // [2][BN * C::LDS_STRIDE]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-  const int64_t nk = km.n;
+  const int64_t nk = (kend - kbeg + C::BK - 1) / C::BK;
 
   // Two register staging sets: the loads of stage t + 1 are issued one
   // iteration before the stage is stored to LDS, so each global load has two
@@ -321,17 +294,16 @@ __device__ __forceinline__ void generic_mainloop_km(const GemmParams& p, const A
     u32x4v b[C::B_CHUNKS];
   };
   Stage st0, st1;
-  typename ALoader::Row arow[C::A_CHUNKS];
+  int64_t arow[C::A_CHUNKS];
 #pragma unroll
-  for (int i = 0; i < C::A_CHUNKS; ++i) arow[i] = aload.row(m0 + (tid + C::THREADS * i) / C::KCH);
+  for (int i = 0; i < C::A_CHUNKS; ++i) arow[i] = m0 + (tid + C::THREADS * i) / C::KCH;
   static_assert(C::THREADS % C::KCH == 0, "a thread keeps one chunk column");
   const int kch = 16 * (tid % C::KCH);  // the K offset of every A chunk this thread loads
   auto gload = [&](Stage& st, int64_t t) __attribute__((always_inline)) {
-    const int64_t k0 = km.k(t);
-    const typename ALoader::KState ks = aload.kstate(k0 + kch);  // once per stage: shared by the thread's rows
+    const int64_t k0 = kbeg + t * C::BK;
 #pragma unroll
     for (int i = 0; i < C::A_CHUNKS; ++i) {
-      const Chunk16 v = aload.load(arow[i], ks);
+      const Chunk16 v = aload.load(arow[i], k0 + kch);
       st.a[i] = u32x4v{v.w[0], v.w[1], v.w[2], v.w[3]};
     }
 #pragma unroll
@@ -389,11 +361,10 @@ __device__ __forceinline__ void generic_mainloop_km(const GemmParams& p, const A
   constexpr int SPREAD = 2 * NLD <= NMF ? 2 : 1;
   auto iter = [&](int64_t t, int buf, Stage& next, Stage& far) __attribute__((always_inline)) {
     if constexpr (NLD <= (NMF + SPREAD - 1) / SPREAD) {
-      const int64_t k0 = km.k(t + 2);
-      const typename ALoader::KState ks = aload.kstate(k0 + kch);
+      const int64_t k0 = kbeg + (t + 2) * C::BK;
       auto load = [&](int q) __attribute__((always_inline)) {
         if (q < C::A_CHUNKS) {
-          const Chunk16 v = aload.load(arow[q], ks);
+          const Chunk16 v = aload.load(arow[q], k0 + kch);
           far.a[q] = u32x4v{v.w[0], v.w[1], v.w[2], v.w[3]};
         } else {
           const int c = tid + C::THREADS * (q - C::A_CHUNKS);
@@ -437,13 +408,6 @@ __device__ __forceinline__ void generic_mainloop_km(const GemmParams& p, const A
     iter(t + 1, 1, st0, st1);
   }
   if (t < nk) iter(t, 0, st1, st0);
-}
-
-template <class C, class ALoader, class BLoader>
-__device__ __forceinline__ void generic_mainloop(const GemmParams& p, const ALoader& aload, const BLoader& bload,
-                                                 int8_t* lds, int64_t m0, int64_t n0, int64_t kbeg, int64_t kend,
-                                                 v16i (&acc)[C::IT][C::JT]) {
-  generic_mainloop_km<C>(p, aload, bload, lds, m0, n0, KRange{kbeg, C::BK, (kend - kbeg + C::BK - 1) / C::BK}, acc);
 }
 
 template <class C, bool FAST, class ALoader>

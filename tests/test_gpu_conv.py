@@ -101,15 +101,15 @@ GEOMETRIES = [
     (4, 8, 5, 7, 16, 3, 1, 1, 0),    # 3 x 1 kernel, no padding
     (3, 8, 7, 7, 16, 3, 3, 1, 0),    # valid 3 x 3
     (3, 24, 6, 6, 48, 3, 3, 1, 1),   # K = 432: a part K stage; 24 input channels: a part column tile
-    (2, 8, 8, 8, 16, 6, 6, 1, 2),    # 36 taps: the general grad_X gather at stride 1
+    (2, 8, 8, 8, 16, 6, 6, 1, 2),    # 36 taps
 ]
 
 
 IMPLICIT_GEOMETRIES = [
-    # stride 1 with enough output pixels per grid row: grad_W on the zero-halo grid
+    # larger images at stride 1: several 128-pixel stages per sample
     (3, 8, 24, 28, 16, 1, 3, 1, 1),   # 1 x 3 kernel, rectangular image
     (3, 8, 28, 30, 16, 3, 1, 1, 1),   # 3 x 1 kernel
-    (2, 24, 14, 14, 48, 3, 3, 1, 1),  # part K stage, part column tile, byte-wise grid copies
+    (2, 24, 14, 14, 48, 3, 3, 1, 1),  # part stages, part column tile
     (2, 8, 30, 30, 16, 2, 2, 1, 0),   # even kernel, no padding
 ]
 
@@ -229,16 +229,16 @@ def exact_conv_grads(X, W, G, stride, pad):
 
 
 GRID_GEOMS = [
-    (128, 64, 56, 64, 3, 1, 1),     # the 56 x 56 layer at full size (implicit grad_W, word-aligned rows)
-    (150, 16, 9, 32, 3, 2, 1),      # more slots per input pixel than one tile
+    (128, 64, 56, 64, 3, 1, 1),     # the 56 x 56 layer at full size
+    (150, 16, 9, 32, 3, 2, 1),      # more slots per input pixel than one unit of 64
     (40, 3, 32, 64, 7, 2, 3),       # stem-like: 7 x 7, stride 2, three channels
     (24, 32, 14, 48, 1, 2, 0),      # 1 x 1, stride 2
-    (8, 16, 11, 16, 5, 1, 2),       # 5 x 5 (explicit im2col: the grid would be too sparse)
-    (6, 8, 14, 16, 3, 1, 1),        # implicit grad_W, 14-byte rows (byte-wise grid copies)
-    (4, 16, 28, 32, 3, 1, 1),       # implicit, 28 x 28
-    (3, 8, 16, 16, 1, 1, 0),        # implicit 1 x 1: one grid copy
-    (2, 8, 44, 16, 5, 1, 2),        # implicit 5 x 5: five copies, K offsets up to 4 grid rows
-    (3, 8, 16, 16, 3, 1, 0),        # implicit valid 3 x 3
+    (8, 16, 11, 16, 5, 1, 2),       # 5 x 5, odd image
+    (6, 8, 14, 16, 3, 1, 1),        # 8 channels, padded to 16
+    (4, 16, 28, 32, 3, 1, 1),       # 28 x 28
+    (3, 8, 16, 16, 1, 1, 0),        # 1 x 1
+    (2, 8, 44, 16, 5, 1, 2),        # 5 x 5 on 44 x 44
+    (3, 8, 16, 16, 3, 1, 0),        # valid 3 x 3
 ]
 
 
